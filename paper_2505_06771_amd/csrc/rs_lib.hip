@@ -272,7 +272,7 @@ __global__ __launch_bounds__(kBlock) void k_barrier(BarrierArgs<T> A) {
       T val = T(0);
       if (act.rows_in_lds) {
         for (int s = 0; s < info.q; ++s)
-          if (sh->act[s] == (a | (b << 8))) val = T(2) * sh->lam[s];
+          if ((int)sh->row[s].x == (a | (b << 8))) val = T(2) * sh->lam[s];
       } else {
         for (int s = 0; s < kQR; ++s)
           if (s < info.q && act.sa[s] == a && act.sb[s] == b) val = T(2) * act.slam[s];

@@ -9,9 +9,10 @@
 // unique. It is found with a dual active-set method in the style of Goldfarb
 // and Idnani (1983) specialised to the identity Hessian:
 //   * bound rows are unit rows, so an active bound simply fixes its coordinate;
-//     the active pairwise rows S enter a Gram system restricted to the free
-//     coordinates, G_S = C_S^free C_S^free^T (q x q, q small), factored by
-//     Cholesky in LDS;
+//     with up to four active pairwise rows S the Gram system over the free
+//     coordinates, G_S = C_S^free C_S^free^T, is factored by Cholesky in
+//     registers; beyond that the inverse Gram matrix of all active rows, bounds
+//     among them, is kept in LDS;
 //   * the start point clips u_nom to the box, which is exactly the state after
 //     adding every violated bound (they are mutually orthogonal);
 //   * each iteration adds the most violated row (normalised violation),
@@ -24,21 +25,39 @@
 // Work split inside the group: lane i owns robot i (its u, bounds, fixed
 // flags and bound multipliers) and the pairs (i, i+k mod N), k = 1..N/2
 // (k = N/2 only for i < N/2), so every pair has exactly one owner and the
-// violation scan costs ceil((N-1)/2) rounds. The q x q algebra is done
-// identically by every lane of the group from group-uniform data.
+// violation scan costs ceil((N-1)/2) rounds. The register loop's algebra is
+// done identically by every lane of the group from group-uniform data; the
+// general solver gives each lane two rows of the inverse.
 #pragma once
 
 #include "rs_device.hpp"
 
 namespace rs {
 
-template <typename T, int G> struct alignas(16) QPScratch {
-  int act[2 * G];           // active pair rows: a | b << 8, a < b
-  T dx[2 * G], dy[2 * G];   // D = p_a - p_b of each active row
-  T lam[2 * G];             // multipliers (objective 1/2 |u - u_nom|^2)
-  T rv[2 * G];              // r = G_S^-1 g
-  T L[(2 * G) * (2 * G + 1) / 2];  // packed lower Cholesky factor of G_S
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// One active row of the general solver, as a vector so that a lane reads it
+// with one LDS access: {id, cx, cy, r}. Its coefficients are (-cx, -cy) at
+// robot ra and (cx, cy) at robot rb, id = ra | rb << 8 (held as a number). A
+// pair row has ra < rb and (cx, cy) = 2 D; an active bound has no second robot
+// (rb = kNoRobot) and (cx, cy) = minus its unit normal. r is a work column:
+// Gram products, then the multiplier direction.
+template <typename T> struct QPRow {
+  typedef T vec __attribute__((ext_vector_type(4)));
 };
+constexpr int kNoRobot = 255;
+constexpr int kQR = 4;  // active rows that the register-resident solver holds
+
+template <typename T, int G> struct alignas(4 * sizeof(T)) QPScratch {
+  typename QPRow<T>::vec row[2 * G];  // active rows
+  T lam[2 * G];                       // multipliers (objective 1/2 |u - u_nom|^2)
+  T H[(2 * G) * (2 * G + 1) / 2];     // inverse Gram matrix of the rows (packed lower)
+};
+// The scratch as an LDS pointer: an out-of-line function that took a generic
+// one would reach it by flat accesses, which also wait for the wavefront's
+// outstanding global stores.
+template <typename T, int G>
+using LdsScratch = __attribute__((address_space(3))) QPScratch<T, G>;
 
 __device__ __forceinline__ int tri(int a, int b) { return (a * (a + 1)) / 2 + b; }
 
@@ -95,31 +114,6 @@ __device__ __forceinline__ void wall_bounds(const CS &C, T px, T py, T &lox, T &
   loy = tmax(-C.vmax, -(C.kb * (myl * myl * myl)));
 }
 
-// Gram entry of active rows s, t over the free coordinates.
-template <typename T>
-__device__ __forceinline__ T gram_entry(int as, int bs, T dxs, T dys, int at, int bt, T dxt,
-                                        T dyt, uint32_t freex, uint32_t freey) {
-  T acc = T(0);
-  // robot shared as the "a" (sign -) or "b" (sign +) end of each row
-  const int ends_s[2] = {as, bs};
-  const int ends_t[2] = {at, bt};
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-#pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      const int r = ends_s[u];
-      if (r == ends_t[v]) {
-        const T sg = (u == v) ? T(4) : T(-4);
-        T dd = T(0);
-        if ((freex >> r) & 1u) dd += dxs * dxt;
-        if ((freey >> r) & 1u) dd += dys * dyt;
-        acc += sg * dd;
-      }
-    }
-  }
-  return acc;
-}
-
 // Stage of the solver that produced the command.
 enum : int {
   kStBox = 0,        // no row violated at the box clip u0
@@ -134,7 +128,7 @@ struct QPInfo {
   int status;  // 0 solved, 1 infeasible, 2 iteration cap / numerical failure
   int iters;   // active-set iterations
   int q;       // active pairwise rows at exit
-  int in_lds;  // 1: the rows are in sh->act / sh->lam (general solver)
+  int in_lds;  // nonzero: the general solver ran
   int stage;   // kSt*: the stage that produced the command
 };
 
@@ -157,284 +151,8 @@ __device__ __forceinline__ void qp_fail_count(unsigned long long *fail, const QP
   if (fail && info.status != 0) atomicAdd(fail + (info.status - 1), 1ull);
 }
 
-// General solver with the active set in LDS (any number of active rows).
-// Every lane of the group must call this together (uniform control flow
-// within the group). `i` is the robot index (lane in group), `on` = i < N. On
-// return (ux, uy) is the command; for status 1 it is the per-coordinate
-// fallback. Used when the register-resident solver below runs out of slots.
-template <typename T, int G>
-__device__ QPInfo qp_solve_lds(QPScratch<T, G> *sh, const SimConst<T> C, int lane, int i, int N,
-                           bool on, T px, T py, T uhx, T uhy, T lox, T hix, T loy, T hiy, T &ux,
-                           T &uy) {
-  const int base = lane & ~(G - 1);
-  const T BIG = big_v<T>();
-  QPInfo info{0, 0, 0, 1, kStGeneral};
-
-  // --- empty box: infeasible, closed-form fallback -------------------------
-  const bool crossed = on && (lox > hix || loy > hiy);
-  bool dead = group_any<G>(crossed, lane);
-
-  // --- start: clip to the box; active bounds fix their coordinate ----------
-  int fx = 0, fy = 0;  // +1 fixed at upper, -1 fixed at lower
-  T mux = T(0), muy = T(0);
-  ux = uhx;
-  uy = uhy;
-  if (on) {
-    if (uhx > hix) { ux = hix; fx = 1; mux = uhx - hix; }
-    else if (uhx < lox) { ux = lox; fx = -1; mux = lox - uhx; }
-    if (uhy > hiy) { uy = hiy; fy = 1; muy = uhy - hiy; }
-    else if (uhy < loy) { uy = loy; fy = -1; muy = loy - uhy; }
-  }
-
-  int q = 0;
-  uint32_t own_act = 0;  // bit k: my rotation-k pair is active
-  const int cap = C.qp_cap > 0 ? C.qp_cap : 8 * N + 32;
-  const int K = N >> 1;
-
-  while (!dead) {
-    // --- most violated constraint ------------------------------------------
-    T best = C.tol_add;
-    int bid = -1;  // pair: a << 4 | b ; bound: 256 + 4 i + 2 coord + (lower)
-    bool coincide = false;
-    if (on) {
-      if (fx == 0) {
-        const T su = ux - hix, sl = lox - ux;
-        if (su > best) { best = su; bid = 256 + 4 * i; }
-        else if (sl > best) { best = sl; bid = 256 + 4 * i + 1; }
-      }
-      if (fy == 0) {
-        const T su = uy - hiy, sl = loy - uy;
-        if (su > best) { best = su; bid = 256 + 4 * i + 2; }
-        else if (sl > best) { best = sl; bid = 256 + 4 * i + 3; }
-      }
-    }
-    for (int k = 1; k <= K; ++k) {
-      const int j = on ? (i + k >= N ? i + k - N : i + k) : 0;
-      const T pxj = __shfl(px, base + j, 64), pyj = __shfl(py, base + j, 64);
-      const T uxj = __shfl(ux, base + j, 64), uyj = __shfl(uy, base + j, 64);
-      const bool mine = on && !(2 * k == N && i >= k) && !((own_act >> k) & 1u);
-      if (mine) {
-        const bool ia = i < j;
-        const T dx = ia ? px - pxj : pxj - px;
-        const T dy = ia ? py - pyj : pyj - py;
-        const T d2 = dx * dx + dy * dy;
-        const T h = d2 - C.rs2;
-        const T bb = C.gamma * (h * h * h);
-        if (C.vmax4 * (tabs(dx) + tabs(dy)) > bb) {
-          const T dux = ia ? uxj - ux : ux - uxj;  // u_b - u_a
-          const T duy = ia ? uyj - uy : uy - uyj;
-          const T s = T(2) * (dx * dux + dy * duy) - bb;
-          if (d2 > T(0)) {
-            const T sn = s * (T(0.35355339059327373) * rsqrt_t(d2));  // s / |c|
-            if (sn > best) {
-              best = sn;
-              bid = (ia ? i : j) << 4 | (ia ? j : i);
-            }
-          } else if (bb < T(0)) {
-            coincide = true;
-          }
-        }
-      }
-    }
-    if (group_any<G>(coincide, lane)) { dead = true; break; }
-    group_argmax<G>(best, bid);
-    if (bid < 0) break;  // optimal
-    if (++info.iters > cap) { info.status = 2; break; }
-
-    // --- constraint p -------------------------------------------------------
-    const bool p_pair = bid < 256;
-    const int pa = p_pair ? (bid >> 4) : ((bid - 256) >> 2);
-    const int pb = p_pair ? (bid & 15) : 0;
-    const int pk = p_pair ? 0 : (((bid - 256) >> 1) & 1);     // bound coordinate
-    const int psig = p_pair ? 0 : (((bid - 256) & 1) ? -1 : 1);  // +1 upper
-    T dpx = T(0), dpy = T(0), bp = T(0);
-    {
-      const T xa = __shfl(px, base + pa, 64), ya = __shfl(py, base + pa, 64);
-      const T xb = __shfl(px, base + pb, 64), yb = __shfl(py, base + pb, 64);
-      if (p_pair) {
-        dpx = xa - xb;
-        dpy = ya - yb;
-        const T h = dpx * dpx + dpy * dpy - C.rs2;
-        bp = C.gamma * (h * h * h);
-      }
-    }
-    T lam_p = T(0);
-    bool added = false;
-    for (int inner = 0; inner < cap && !added; ++inner) {
-      const uint32_t freex = ~group_bits<G>(__ballot(fx != 0), lane);
-      const uint32_t freey = ~group_bits<G>(__ballot(fy != 0), lane);
-      // Gram system of the active rows over the free coordinates
-      bool chol_ok = true;
-      for (int a = 0; a < q && chol_ok; ++a) {
-        const int acta = sh->act[a];
-        const int aa = acta & 255, ab = acta >> 8;
-        const T adx = sh->dx[a], ady = sh->dy[a];
-        for (int b = 0; b <= a; ++b) {
-          const int actb = sh->act[b];
-          T s = gram_entry<T>(aa, ab, adx, ady, actb & 255, actb >> 8, sh->dx[b], sh->dy[b], freex,
-                              freey);
-          for (int k2 = 0; k2 < b; ++k2) s -= sh->L[tri(a, k2)] * sh->L[tri(b, k2)];
-          if (a == b) {
-            if (!(s > T(0))) { chol_ok = false; break; }
-            sh->L[tri(a, a)] = sqrt_t(s);
-          } else {
-            sh->L[tri(a, b)] = s / sh->L[tri(b, b)];
-          }
-        }
-      }
-      if (!chol_ok) { info.status = 2; break; }
-      // g = C_S^free c_p, then r = G_S^-1 g (forward, backward substitution)
-      for (int a = 0; a < q; ++a) {
-        const int acta = sh->act[a];
-        const int aa = acta & 255, ab = acta >> 8;
-        T g;
-        if (p_pair) {
-          g = gram_entry<T>(aa, ab, sh->dx[a], sh->dy[a], pa, pb, dpx, dpy, freex, freey);
-        } else {
-          const T comp = pk ? sh->dy[a] : sh->dx[a];
-          g = (pa == aa) ? T(-2) * comp : ((pa == ab) ? T(2) * comp : T(0));
-          g *= T(psig);
-        }
-        for (int k2 = 0; k2 < a; ++k2) g -= sh->L[tri(a, k2)] * sh->rv[k2];
-        sh->rv[a] = g / sh->L[tri(a, a)];
-      }
-      for (int a = q - 1; a >= 0; --a) {
-        T s = sh->rv[a];
-        for (int k2 = a + 1; k2 < q; ++k2) s -= sh->L[tri(k2, a)] * sh->rv[k2];
-        sh->rv[a] = s / sh->L[tri(a, a)];
-      }
-      // (C_S^T r) and c_p at my robot
-      T crx = T(0), cry = T(0);
-      for (int a = 0; a < q; ++a) {
-        const int acta = sh->act[a];
-        const T ra = sh->rv[a];
-        if (i == (acta & 255)) { crx -= T(2) * sh->dx[a] * ra; cry -= T(2) * sh->dy[a] * ra; }
-        else if (i == (acta >> 8)) { crx += T(2) * sh->dx[a] * ra; cry += T(2) * sh->dy[a] * ra; }
-      }
-      T cpx = T(0), cpy = T(0);
-      if (p_pair) {
-        if (i == pa) { cpx = T(-2) * dpx; cpy = T(-2) * dpy; }
-        else if (i == pb) { cpx = T(2) * dpx; cpy = T(2) * dpy; }
-      } else if (i == pa) {
-        if (pk) cpy = T(psig); else cpx = T(psig);
-      }
-      if (!on) { crx = cry = cpx = cpy = T(0); }
-      const T zx = fx == 0 ? cpx - crx : T(0);
-      const T zy = fy == 0 ? cpy - cry : T(0);
-      const T rfx = fx != 0 ? T(fx) * (cpx - crx) : T(0);
-      const T rfy = fy != 0 ? T(fy) * (cpy - cry) : T(0);
-      const T zz = group_sum<G>(zx * zx + zy * zy);
-      T cpn2;
-      if (p_pair) {
-        T sa = T(0), sb = T(0);
-        if ((freex >> pa) & 1u) sa += dpx * dpx;
-        if ((freey >> pa) & 1u) sa += dpy * dpy;
-        if ((freex >> pb) & 1u) sb += dpx * dpx;
-        if ((freey >> pb) & 1u) sb += dpy * dpy;
-        cpn2 = T(4) * (sa + sb);
-      } else {
-        cpn2 = T(1);
-      }
-      // blocking step t1: active rows first (uniform), then my fixed bounds
-      T t1 = BIG;
-      int drop = -1;  // pair slot, or 1024 + 2 robot + coord for a bound
-      for (int a = 0; a < q; ++a) {
-        const T ra = sh->rv[a];
-        if (ra > C.eps_r) {
-          const T ratio = qdiv(sh->lam[a], ra);
-          if (ratio < t1) { t1 = ratio; drop = a; }
-        }
-      }
-      if (on && fx != 0 && rfx > C.eps_r) {
-        const T ratio = qdiv(mux, rfx);
-        if (ratio < t1 || (ratio == t1 && drop < 0)) { t1 = ratio; drop = 1024 + 2 * i; }
-      }
-      if (on && fy != 0 && rfy > C.eps_r) {
-        const T ratio = qdiv(muy, rfy);
-        if (ratio < t1 || (ratio == t1 && drop < 0)) { t1 = ratio; drop = 1024 + 2 * i + 1; }
-      }
-      group_argmin<G>(t1, drop);
-      // current violation of p
-      T sp;
-      if (p_pair) {
-        const T uxa = __shfl(ux, base + pa, 64), uya = __shfl(uy, base + pa, 64);
-        const T uxb = __shfl(ux, base + pb, 64), uyb = __shfl(uy, base + pb, 64);
-        sp = T(2) * (dpx * (uxb - uxa) + dpy * (uyb - uya)) - bp;
-      } else {
-        const T mine = pk ? (psig > 0 ? uy - hiy : loy - uy) : (psig > 0 ? ux - hix : lox - ux);
-        sp = __shfl(mine, base + pa, 64);
-      }
-      const bool z_ok = zz > C.eps_z * cpn2;
-      const T t2 = z_ok ? qdiv(sp, zz) : BIG;
-      if (drop < 0 && !z_ok) { dead = true; break; }  // no step can restore p
-      const bool full = z_ok && (drop < 0 || t2 <= t1);
-      const T t = full ? t2 : t1;
-      if (z_ok) {
-        ux -= t * zx;
-        uy -= t * zy;
-      }
-      for (int a = 0; a < q; ++a) sh->lam[a] = sh->lam[a] - t * sh->rv[a];
-      if (on) {
-        mux -= t * rfx;
-        muy -= t * rfy;
-      }
-      lam_p += t;
-      if (full) {
-        if (p_pair) {
-          if (q >= 2 * G) { info.status = 2; break; }
-          sh->act[q] = pa | (pb << 8);
-          sh->dx[q] = dpx;
-          sh->dy[q] = dpy;
-          sh->lam[q] = lam_p;
-          ++q;
-          int owner, kk;
-          pair_owner(pa, pb, N, owner, kk);
-          if (i == owner) own_act |= 1u << kk;
-        } else if (i == pa) {
-          if (pk) { fy = psig; muy = lam_p; uy = psig > 0 ? hiy : loy; }
-          else { fx = psig; mux = lam_p; ux = psig > 0 ? hix : lox; }
-        }
-        added = true;
-      } else if (drop >= 1024) {
-        const int r = (drop - 1024) >> 1, c = (drop - 1024) & 1;
-        if (i == r) {
-          if (c) { fy = 0; muy = T(0); } else { fx = 0; mux = T(0); }
-        }
-      } else {
-        const int act = sh->act[drop];
-        int owner, kk;
-        pair_owner(act & 255, act >> 8, N, owner, kk);
-        if (i == owner) own_act &= ~(1u << kk);
-        for (int a = drop; a + 1 < q; ++a) {
-          sh->act[a] = sh->act[a + 1];
-          sh->dx[a] = sh->dx[a + 1];
-          sh->dy[a] = sh->dy[a + 1];
-          sh->lam[a] = sh->lam[a + 1];
-        }
-        --q;
-      }
-      if (++info.iters > cap) { info.status = 2; break; }
-    }
-    if (info.status == 2 || dead) break;
-  }
-
-  if (dead) {
-    info.status = 1;
-    if (on) {
-      ux = lox <= hix ? tmin(tmax(uhx, lox), hix) : T(0.5) * (lox + hix);
-      uy = loy <= hiy ? tmin(tmax(uhy, loy), hiy) : T(0.5) * (loy + hiy);
-    }
-  }
-  info.q = dead ? 0 : q;
-  return info;
-}
-
-}  // namespace rs
-
-namespace rs {
-
 // ---------------------------------------------------------------------------
-// Register-resident solver (the hot path). Same method as qp_solve_lds, but
+// Register-resident solver (the hot path):
 //  * the active pairwise rows live in kQR group-uniform register slots, so
 //    the q x q Gram/Cholesky algebra is straight-line code on registers;
 //  * a lane owns the pairs (i, (i+K) mod G), K = 1..G/2 (K = G/2 only for
@@ -443,14 +161,13 @@ namespace rs {
 //  * every cross-lane quantity (argmax with the row's data as payload, |z|^2,
 //    the violation of the entering row, the blocking step) is a DPP butterfly
 //    over the group: no LDS traffic at all.
-// When a row must enter while all slots are taken, or the Gram system loses
-// positive definiteness, the general solver restarts from scratch.
+// When a row must enter while all slots are taken, the general solver carries
+// on from there; when the Gram system loses positive definiteness, it starts
+// again from the box clip.
 // ---------------------------------------------------------------------------
-constexpr int kQR = 4;
-
 template <typename T> struct QPActive {
   int q;
-  int rows_in_lds;  // 1: the rows are in sh->act / sh->lam (active-set loops)
+  int rows_in_lds;  // 1: the rows are in sh->row / sh->lam (active-set loops)
   int sa[kQR], sb[kQR];
   T slam[kQR];
 };
@@ -520,8 +237,502 @@ template <int G> __device__ __forceinline__ void pair_owner_g(int a, int b, int 
 // reading it back would wait for every outstanding store of the wavefront).
 template <typename T> struct QPLoopOut {
   T ux, uy;
-  int status, iters, q, in_lds;
+  int status, iters, q;
+  int in_lds;  // the general solver ran: 1 from the clip, 2 from the loop's active set
 };
+
+// General solver: the dual active-set method for any number of active rows,
+// bounds and pairs alike (at most 2N rows are independent). The inverse H of
+// the active rows' Gram matrix is kept explicitly in LDS (packed symmetric):
+// lane i of the group owns slots i and i + G, so the multiplier direction
+// r = H (C c_p) is one row product per lane with no serial substitution, a row
+// entering is a rank-one update of H (its Schur complement is |z|^2) and a row
+// leaving another; the last slot then moves into the gap. It is bound by the
+// latency of its few hundred instructions and six LDS round trips a step, in
+// the few wavefronts that need it. Refactoring the Gram system serially on
+// every step instead, from scratch, took 1.53 ms for one env_step of 16384
+// envs x 16 robots, a dense eighth of them, and 0.32 ms for 8192 x 12
+// certificates; this takes 0.21 and 0.06 ms.
+//
+// Explicit updates of H lose digits over many steps, so once no row is
+// violated the command and the multipliers are formed again from the active
+// rows (one residual correction with H, which leaves rounding of the residual
+// itself) and scanned again; a correction that does not close the residual
+// rebuilds H from the rows.
+//
+// Entry (qp_handover, written by the register loop): the problem and the
+// active bounds of every lane, and with `carry` the loop's q0 pair rows, the
+// entering row and its multiplier; (ux, uy) is the command of that active
+// set. Without `carry` it starts from the box clip. `iters` counts on from the
+// caller's. Every lane of the group calls it together; the rows stay in
+// sh->row / sh->lam.
+// What the register loop leaves in the group's scratch for the general solver:
+// twelve values per lane at the end of it (value c of lane i at c * G + i) and,
+// ahead of them, rows 0..3 {id, cx, cy, multiplier}, row 4 the entering row
+// {id, cx, cy, rhs} and its multiplier. With the problem in LDS the register
+// loop can end in a tail call of the general solver, which leaves it a leaf
+// function: as an ordinary caller it saved more registers on every entry (1%
+// of the headline rollout's time), and a second call site in the step loop
+// cost that loop 2 to 4%.
+constexpr int kHandover = 12;
+template <typename T, int G>
+__device__ __forceinline__ __attribute__((address_space(3))) T *handover(LdsScratch<T, G> *sh) {
+  static_assert(G == 2 || sizeof(QPScratch<T, G>) / sizeof(T) >= 24 + kHandover * G, "rows fit");
+  static_assert(sizeof(QPScratch<T, G>) / sizeof(T) >= kHandover * G, "lanes fit");
+  return (__attribute__((address_space(3))) T *)(sh + 1) - kHandover * G;
+}
+
+template <typename T, int G>
+__device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane, int N, bool carry,
+                                                 QPLoopOut<T> &out, T rs2, T gamma, T vmax4,
+                                                 T tol_add, T eps_z, T eps_r, int qp_cap) {
+  constexpr int KH = G / 2;
+  constexpr int S = 2;  // slots per lane: i and i + G
+  const T BIG = big_v<T>();
+  typedef typename QPRow<T>::vec Row;
+  typedef __attribute__((address_space(3))) Row LdsRow;
+  typedef __attribute__((address_space(3))) T LdsT;
+  LdsRow *rows = sh->row;
+  LdsT *lam = sh->lam, *H = sh->H;
+  auto work = [&](int k) -> LdsT & { return ((LdsT *)(rows + k))[3]; };
+  const int i = lane & (G - 1);
+  const bool on = i < N;
+  const int gbase = lane & ~(G - 1);
+  const int cap = qp_cap > 0 ? qp_cap : 8 * N + 32;
+  // --- what the register loop left ---------------------------------------------
+  const LdsT *hv = handover<T, G>(sh) + i;
+  const T px = hv[0], py = hv[G], uhx = hv[2 * G], uhy = hv[3 * G];
+  const T lox = hv[4 * G], hix = hv[5 * G], loy = hv[6 * G], hiy = hv[7 * G];
+  int fx = (int)hv[8 * G], fy = (int)hv[9 * G];
+  T mux = hv[10 * G], muy = hv[11 * G];
+  Row p = (Row){T(0), T(0), T(0), T(0)};  // the entering row
+  T lam_p = T(0), hl = T(0);              // its multiplier; lane k < 4: row k's
+  if constexpr (G > 2) {
+    if (carry) {
+      p = rows[kQR];
+      lam_p = ((LdsT *)(rows + kQR + 1))[0];
+      hl = work(i & (kQR - 1));
+    }
+  }
+  T ux = out.ux, uy = out.uy;
+  int q0 = out.q;
+  const int iters0 = carry ? 0 : out.iters;  // of the abandoned attempt
+  out.iters -= iters0;
+  if (!carry) {  // the box clip, its active bounds fixing their coordinate
+    q0 = 0;
+    ux = uhx;
+    uy = uhy;
+    fx = fy = 0;
+    mux = muy = T(0);
+    if (on) {
+      if (uhx > hix) { ux = hix; fx = 1; mux = uhx - hix; }
+      else if (uhx < lox) { ux = lox; fx = -1; mux = lox - uhx; }
+      if (uhy > hiy) { uy = hiy; fy = 1; muy = uhy - hiy; }
+      else if (uhy < loy) { uy = loy; fy = -1; muy = loy - uhy; }
+    }
+  }
+  wave_lds_fence();
+  if (i < q0) lam[i] = hl;
+  // --- geometry of the owned pairs (the scan's formulas) ----------------------
+  T cdx[KH], cdy[KH], cb[KH], crn[KH];
+  int cpid[KH];
+  static_for<1, KH + 1>([&](auto kc) {
+    constexpr int K = decltype(kc)::value;
+    const T pxj = grot<G, K>(px, lane), pyj = grot<G, K>(py, lane);
+    const int j = (i + K) & (G - 1);
+    const bool valid = on && j < N && !(2 * K == G && i >= KH);
+    const bool ia = i < j;
+    const T dx = ia ? px - pxj : pxj - px;
+    const T dy = ia ? py - pyj : pyj - py;
+    const T d2 = dx * dx + dy * dy;
+    const T h = d2 - rs2;
+    const T bb = gamma * (h * h * h);
+    const bool cand = valid && (vmax4 * (tabs(dx) + tabs(dy)) > bb);
+    cdx[K - 1] = dx;
+    cdy[K - 1] = dy;
+    cb[K - 1] = bb;
+    crn[K - 1] = d2 > T(0) ? T(0.35355339059327373) * rsqrt_t(d2) : T(0);
+    cpid[K - 1] = (cand && d2 > T(0)) ? ((ia ? i : j) << 4 | (ia ? j : i)) : -1;
+  });
+  uint32_t own_act = 0;  // bit K: my rotation-K pair is active
+
+  // --- active bounds into the slots after the pairs, then H row by row --------
+  int q;
+  {
+    const uint32_t bx = group_bits<G>(__ballot(fx != 0), lane);
+    const uint32_t by = group_bits<G>(__ballot(fy != 0), lane);
+    const uint32_t below = (1u << i) - 1u;
+    const int qx = q0 + __popc(bx);
+    const int sx = q0 + __popc(bx & below), sy = qx + __popc(by & below);
+    q = qx + __popc(by);
+    if (q > 2 * G) {
+      out = QPLoopOut<T>{ux, uy, 2, out.iters + iters0, 0, out.in_lds};
+      return;
+    }
+    if (fx != 0) {
+      rows[sx] = (Row){T(i | kNoRobot << 8), T(-fx), T(0), T(0)};
+      lam[sx] = mux;
+    }
+    if (fy != 0) {
+      rows[sy] = (Row){T(i | kNoRobot << 8), T(0), T(-fy), T(0)};
+      lam[sy] = muy;
+    }
+    wave_lds_fence();
+    for (int s = 0; s < q0; ++s) {
+      const int id = (int)rows[s].x;
+      int owner, kk;
+      pair_owner_g<G>(id & 255, id >> 8, owner, kk);
+      if (i == owner) own_act |= 1u << kk;
+    }
+  }
+  // product of H's row k with the work column of the first n rows
+  auto hdot = [&](int k, int n) {
+    T acc = T(0);
+    int idx = tri(k, 0);
+#pragma unroll 4
+    for (int b = 0; b < n; ++b) {
+      acc += H[idx] * work(b);
+      idx += b < k ? 1 : b + 1;
+    }
+    return acc;
+  };
+  // r = H (C c) over the first n rows for the row (ra, rb, cx, cy); r is left
+  // in the work column and, for my slots, in rk; (zx, zy): the part of the
+  // row orthogonal to them at my robot, zz = |z|^2
+  T rk[S];
+  auto direction = [&](int n, int ra, int rb, T cx, T cy, T &zx, T &zy, T &zz) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int k = i + s * G;
+      if (k < n) {
+        const Row w = rows[k];
+        const int wa = (int)w.x & 255, wb = (int)w.x >> 8;
+        const int m = (wa == ra) - (wa == rb) - (wb == ra) + ((wb == rb) & (wb != kNoRobot));
+        work(k) = T(m) * (w.y * cx + w.z * cy);
+      }
+    }
+    wave_lds_fence();
+#pragma unroll
+    for (int s = 0; s < S; ++s) rk[s] = i + s * G < n ? hdot(i + s * G, n) : T(0);
+    wave_lds_fence();
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+      if (i + s * G < n) work(i + s * G) = rk[s];
+    wave_lds_fence();
+    const int sg = (i == rb) - (i == ra);
+    zx = T(sg) * cx;
+    zy = T(sg) * cy;
+#pragma unroll 4
+    for (int a = 0; a < n; ++a) {
+      const Row w = rows[a];
+      const T f = T((i == ((int)w.x >> 8)) - (i == ((int)w.x & 255))) * w.w;
+      zx -= f * w.y;
+      zy -= f * w.z;
+    }
+    zz = gsum<G>(zx * zx + zy * zy);
+  };
+  // H of n rows -> n + 1 rows, from r (rk, work column) and zz of the new one
+  auto grow = [&](int n, T zz) {
+    const T iz = T(1) / zz;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int k = i + s * G;
+      if (k < n) {
+        const T f = rk[s] * iz;
+#pragma unroll 4
+        for (int b = 0; b <= k; ++b) H[tri(k, b)] += f * work(b);
+        H[tri(n, k)] = -f;
+      }
+    }
+    if (i == 0) H[tri(n, n)] = iz;
+    wave_lds_fence();
+  };
+  // H of the first n rows of the table; false when one depends on the others
+  auto rebuild = [&](int n) {
+    bool indep = true;
+    for (int s = 0; s < n && indep; ++s) {
+      const Row w = rows[s];
+      const int wb = (int)w.x >> 8;
+      T zx, zy, zz;
+      direction(s, (int)w.x & 255, wb, w.y, w.z, zx, zy, zz);
+      const T n2 = (wb == kNoRobot ? T(1) : T(2)) * (w.y * w.y + w.z * w.z);
+      indep = zz > T(0.01) * eps_z * n2;
+      if (indep) grow(s, zz);
+    }
+    return indep;
+  };
+  // command and multipliers from the active rows: one correction of the
+  // multipliers by H times the rows' residuals; returns the largest residual
+  // that was left after it
+  auto refine = [&]() {
+    T left = T(0);
+    for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        if (i + s * G < q) work(i + s * G) = lam[i + s * G];
+      wave_lds_fence();
+      T vx = uhx, vy = uhy;
+#pragma unroll 4
+      for (int a = 0; a < q; ++a) {
+        const Row w = rows[a];
+        const T f = T((i == ((int)w.x >> 8)) - (i == ((int)w.x & 255))) * w.w;
+        vx -= f * w.y;
+        vy -= f * w.z;
+      }
+      ux = on ? vx : ux;
+      uy = on ? vy : uy;
+      const T bx = fx > 0 ? hix : lox, by = fy > 0 ? hiy : loy;
+      T e[S], worst = T(0);
+      wave_lds_fence();
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const int k = i + s * G;
+        const Row w = rows[k < q ? k : 0];
+        const int ra = (int)w.x & 255, rb = (int)w.x >> 8;
+        const bool bound = rb == kNoRobot;
+        const int la = gbase + (ra & (G - 1)), lb = gbase + (rb & (G - 1));
+        const T uax = __shfl(ux, la, 64), uay = __shfl(uy, la, 64);
+        const T ubx = __shfl(ux, lb, 64), uby = __shfl(uy, lb, 64);
+        const T bax = __shfl(bx, la, 64), bay = __shfl(by, la, 64);
+        const T d2 = T(0.25) * (w.y * w.y + w.z * w.z);
+        const T h = d2 - rs2;
+        const T beta = gamma * (h * h * h);
+        e[s] = bound ? w.y * (bax - uax) + w.z * (bay - uay)
+                     : w.y * (ubx - uax) + w.z * (uby - uay) - beta;
+        e[s] = k < q ? e[s] : T(0);
+        worst = tmax(worst, tabs(e[s]));
+      }
+      left = gmax<G>(worst);
+      if (pass == 1) break;
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        if (i + s * G < q) work(i + s * G) = e[s];
+      wave_lds_fence();
+      T dl[S];
+#pragma unroll
+      for (int s = 0; s < S; ++s) dl[s] = i + s * G < q ? hdot(i + s * G, q) : T(0);
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        if (i + s * G < q) lam[i + s * G] += dl[s];
+      wave_lds_fence();
+    }
+    if (fx != 0) ux = fx > 0 ? hix : lox;
+    if (fy != 0) uy = fy > 0 ? hiy : loy;
+    return left;
+  };
+
+  bool dead = false;
+  bool settled = false;  // the command was formed from the rows since they last changed
+  if (!rebuild(q)) {
+    out = QPLoopOut<T>{ux, uy, 2, out.iters + iters0, 0, out.in_lds};
+    return;
+  }
+  // the entering row: a pair (ra < rb, 2 D) or a bound
+  bool pend = carry;
+  int ra = (int)p.x & 255, rb = (int)p.x >> 8;
+  T cx = p.y, cy = p.z, rhs = p.w;
+  while (true) {
+    if (!pend) {
+      // --- most violated row (normalised), its data as the argmax's payload ---
+      T best = tol_add, bcx = T(0), bcy = T(0), bb = T(0);
+      int bid = -1;  // pair: a << 4 | b; bound: 256 + 4 robot + 2 coordinate + lower
+      if (on) {
+        if (fx == 0) {
+          const T su = ux - hix, sl = lox - ux;
+          if (su > best) { best = su; bid = 256 + 4 * i; }
+          else if (sl > best) { best = sl; bid = 256 + 4 * i + 1; }
+        }
+        if (fy == 0) {
+          const T su = uy - hiy, sl = loy - uy;
+          if (su > best) { best = su; bid = 256 + 4 * i + 2; }
+          else if (sl > best) { best = sl; bid = 256 + 4 * i + 3; }
+        }
+        if (bid >= 0) {
+          const T sg = (bid & 1) ? T(1) : T(-1);  // minus the unit normal
+          bcx = (bid & 2) ? T(0) : sg;
+          bcy = (bid & 2) ? sg : T(0);
+          bb = (bid & 2) ? ((bid & 1) ? -loy : hiy) : ((bid & 1) ? -lox : hix);
+        }
+      }
+      static_for<1, KH + 1>([&](auto kc) {
+        constexpr int K = decltype(kc)::value;
+        const T uxj = grot<G, K>(ux, lane), uyj = grot<G, K>(uy, lane);
+        if (cpid[K - 1] >= 0 && !((own_act >> K) & 1u)) {
+          const bool ia = i < ((i + K) & (G - 1));
+          const T dux = ia ? uxj - ux : ux - uxj;
+          const T duy = ia ? uyj - uy : uy - uyj;
+          const T sn = (T(2) * (cdx[K - 1] * dux + cdy[K - 1] * duy) - cb[K - 1]) * crn[K - 1];
+          if (sn > best) {
+            best = sn;
+            bid = cpid[K - 1];
+            bcx = T(2) * cdx[K - 1];
+            bcy = T(2) * cdy[K - 1];
+            bb = cb[K - 1];
+          }
+        }
+      });
+      gargmax_payload<G>(best, bid, bcx, bcy, bb);
+      if (bid < 0) {
+        if (settled) break;  // optimal
+        bool good = refine() <= tol_add;
+        if (!good) good = rebuild(q) && refine() <= T(8) * tol_add;
+        if (!good) { out.status = 2; break; }
+        settled = true;
+        continue;
+      }
+      if (++out.iters > cap) { out.status = 2; break; }
+      ra = bid < 256 ? bid >> 4 : (bid - 256) >> 2;
+      rb = bid < 256 ? bid & 15 : kNoRobot;
+      cx = bcx;
+      cy = bcy;
+      rhs = bb;
+      lam_p = T(0);
+      pend = true;
+    }
+    // --- one step toward the entering row -------------------------------------
+    const bool p_pair = rb != kNoRobot;
+    T zx, zy, zz;
+    direction(q, ra, rb, cx, cy, zx, zy, zz);
+    const int sg = (i == rb) - (i == ra);
+    const T sp = gsum<G>(on ? T(sg) * (cx * ux + cy * uy) : T(0)) - rhs;
+    // blocking row: the first active multiplier to reach zero
+    T t1 = BIG;
+    int drop = -1;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int k = i + s * G;
+      const T ratio = k < q ? qdiv(lam[k], rk[s]) : T(0);
+      const bool ok = k < q && rk[s] > eps_r && ratio < t1;
+      t1 = ok ? ratio : t1;
+      drop = ok ? k : drop;
+    }
+    gargmin<G>(t1, drop);
+    const T n2 = (p_pair ? T(2) : T(1)) * (cx * cx + cy * cy);
+    const bool z_ok = zz > eps_z * n2;
+    const T t2 = z_ok ? qdiv(sp, zz) : BIG;
+    if (drop < 0 && !z_ok) { dead = true; break; }  // no step can restore the row
+    const bool full = z_ok && (drop < 0 || t2 <= t1);
+    const T t = full ? t2 : t1;
+    if (full && q == 2 * G) { out.status = 2; break; }
+    if (z_ok) {
+      ux -= t * zx;
+      uy -= t * zy;
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+      if (i + s * G < q) lam[i + s * G] -= t * rk[s];
+    lam_p += t;
+    settled = false;
+    if (full) {
+      grow(q, zz);
+      if (i == 0) {
+        rows[q] = (Row){T(ra | rb << 8), cx, cy, T(0)};
+        lam[q] = lam_p;
+      }
+      wave_lds_fence();
+      ++q;
+      if (p_pair) {
+        int owner, kk;
+        pair_owner_g<G>(ra, rb, owner, kk);
+        if (i == owner) own_act |= 1u << kk;
+      } else if (i == ra) {
+        // (cx, cy) is minus the normal: negative at an upper bound
+        if (cx != T(0)) { fx = cx < T(0) ? 1 : -1; ux = cx < T(0) ? hix : lox; }
+        else { fy = cy < T(0) ? 1 : -1; uy = cy < T(0) ? hiy : loy; }
+      }
+      pend = false;
+    } else {
+      // --- release slot `drop`; the last slot takes its place ------------------
+      const Row w = rows[drop];
+      const int wa = (int)w.x & 255, wb = (int)w.x >> 8;
+      if (wb == kNoRobot) {
+        if (i == wa) {
+          if (w.y != T(0)) fx = 0; else fy = 0;
+        }
+      } else {
+        int owner, kk;
+        pair_owner_g<G>(wa, wb, owner, kk);
+        if (i == owner) own_act &= ~(1u << kk);
+      }
+      const int last = q - 1;
+      const T ihd = T(1) / H[tri(drop, drop)];
+      T hk[S];
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const int k = i + s * G;
+        hk[s] = k < q ? H[k >= drop ? tri(k, drop) : tri(drop, k)] : T(0);
+      }
+      wave_lds_fence();
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        if (i + s * G < q) work(i + s * G) = hk[s];
+      wave_lds_fence();
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const int k = i + s * G;
+        if (k < q) {
+          const T f = hk[s] * ihd;
+#pragma unroll 4
+          for (int b = 0; b <= k; ++b) H[tri(k, b)] -= f * work(b);
+        }
+      }
+      wave_lds_fence();
+      if (drop != last) {
+        T mv[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const int k = i + s * G;
+          mv[s] = k < last ? H[k == drop ? tri(last, last) : tri(last, k)] : T(0);
+        }
+        wave_lds_fence();
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const int k = i + s * G;
+          if (k < last) H[k >= drop ? tri(k, drop) : tri(drop, k)] = mv[s];
+        }
+        if (i == 0) {
+          rows[drop] = rows[last];
+          lam[drop] = lam[last];
+        }
+        wave_lds_fence();
+      }
+      q = last;
+    }
+    if (++out.iters > cap) { out.status = 2; break; }
+  }
+
+  if (dead) {
+    out.status = 1;
+    q = 0;
+    if (on) {
+      ux = lox <= hix ? tmin(tmax(uhx, lox), hix) : T(0.5) * (lox + hix);
+      uy = loy <= hiy ? tmin(tmax(uhy, loy), hiy) : T(0.5) * (loy + hiy);
+    }
+  }
+  out.ux = ux;
+  out.uy = uy;
+  out.q = q;
+  out.iters += iters0;
+}
+
+// Tail of the register loop for a wavefront in which some group needs the
+// general solver; the others' results pass through.
+// It has the register loop's signature (what a tail call needs here) and takes
+// the result so far in uhx, uhy (command), i (in_lds, status and rows, a byte
+// each) and fpa (iterations).
+template <typename T, int G>
+__device__ __noinline__ QPLoopOut<T> qp_general(LdsScratch<T, G> *sh, int lane, int packed, int N,
+                                                bool on, T px, T py, T ux, T uy, T lox, T hix,
+                                                T loy, T hiy, bool seed, int iters, int fpb, T fl1,
+                                                T fdx, T fdy, T rs2, T gamma, T vmax4, T tol_add,
+                                                T eps_z, T eps_r, int qp_cap, bool want_rows) {
+  QPLoopOut<T> out{ux, uy, (packed >> 8) & 255, iters, packed >> 16, packed & 255};
+  if (out.in_lds != 0)
+    qp_general_solve<T, G>(sh, lane, N, out.in_lds == 2, out, rs2, gamma, vmax4, tol_add, eps_z,
+                           eps_r, qp_cap);
+  __builtin_amdgcn_s_setprio(0);
+  return out;
+}
 
 // The active-set loop, kept out of line: it runs for the few environments the
 // closed-form stages leave, and inlined its registers would weigh on every
@@ -529,10 +740,10 @@ template <typename T> struct QPLoopOut {
 // starts from the box clip or, with `seed`, from the one-row solution of row
 // (fpa, fpb) with multiplier fl1 (fdx, fdy = p_a - p_b). Every lane of the
 // group calls it together. Only scalars cross the call. With want_rows the
-// active rows and their multipliers are left in sh->act / sh->lam (as the
+// active rows and their multipliers are left in sh->row / sh->lam (as the
 // general solver leaves them) for the caller to read.
 template <typename T, int G>
-__device__ __noinline__ QPLoopOut<T> qp_active_set(QPScratch<T, G> *sh, int lane, int i, int N,
+__device__ __noinline__ QPLoopOut<T> qp_active_set(LdsScratch<T, G> *sh, int lane, int i, int N,
                                                    bool on, T px, T py, T uhx, T uhy, T lox,
                                                    T hix, T loy, T hiy, bool seed, int fpa,
                                                    int fpb, T fl1, T fdx, T fdy, T rs2, T gamma,
@@ -575,6 +786,10 @@ __device__ __noinline__ QPLoopOut<T> qp_active_set(QPScratch<T, G> *sh, int lane
     crn[K - 1] = d2 > T(0) ? T(0.35355339059327373) * rsqrt_t(d2) : T(0);
     cpid[K - 1] = (cand && d2 > T(0)) ? ((ia ? i : j) << 4 | (ia ? j : i)) : -1;
   });
+  // the projection points are not needed again here: into the hand-over's
+  // place now (clear of the row handed in through H), out of the registers
+  handover<T, G>(sh)[i] = px;
+  handover<T, G>(sh)[G + i] = py;
   // --- start: clip to the box; active bounds fix their coordinate ----------
   int fx = 0, fy = 0;
   T mux = T(0), muy = T(0);
@@ -610,7 +825,7 @@ __device__ __noinline__ QPLoopOut<T> qp_active_set(QPScratch<T, G> *sh, int lane
     for (int b = 0; b <= a; ++b) L[tri(a, b)] = T(0);
   }
   uint32_t own_act = 0;
-  bool restart = false;
+  bool restart = false, carry = false;  // carry: restart from this state, p entering
 
   if (seed) {
     // row (fpa, fpb) active with multiplier fl1; its robots' coordinates are
@@ -663,7 +878,7 @@ __device__ __noinline__ QPLoopOut<T> qp_active_set(QPScratch<T, G> *sh, int lane
     if constexpr (std::is_same<T, float>::value) {
       // FP32: the caller hands over the row its closed-form stages found most
       // violated at this start: with a seed, through the group's scratch
-      // (L[0..3]: row id a << 4 | b, D = p_a - p_b, b); without one, the rows
+      // (H[0..3]: row id a << 4 | b, D = p_a - p_b, b); without one, the rows
       // of a rejected guess (or four or more rows violated at u0) start at
       // u0, where the row (fpa, fpb, fdx, fdy) is the most violated one, its
       // b from the same formula as the geometry above. It enters without a scan once its
@@ -677,7 +892,7 @@ __device__ __noinline__ QPLoopOut<T> qp_active_set(QPScratch<T, G> *sh, int lane
         const T rh = rd2 - C.rs2;
         T rb = C.gamma * (rh * rh * rh);
         if (seed) {
-          const float4 pr = reinterpret_cast<const float4 *>(sh->L)[0];
+          const floatx4 pr = *(const __attribute__((address_space(3))) floatx4 *)sh->H;
           pid = __float_as_int(pr.x);
           rdx = pr.y;
           rdy = pr.z;
@@ -854,7 +1069,7 @@ __device__ __noinline__ QPLoopOut<T> qp_active_set(QPScratch<T, G> *sh, int lane
     if (drop < 0 && !z_ok) { dead = true; break; }
     const bool full = z_ok && (drop < 0 || t2 <= t1);
     const T t = full ? t2 : t1;
-    if (full && p_pair && q == kQR) { restart = true; break; }  // no slot left
+    if (full && p_pair && q == kQR) { restart = carry = true; break; }  // no slot left
     const T tz = z_ok ? t : T(0);
     ux -= tz * zx;
     uy -= tz * zy;
@@ -926,25 +1141,36 @@ __device__ __noinline__ QPLoopOut<T> qp_active_set(QPScratch<T, G> *sh, int lane
   }
 
   QPLoopOut<T> out;
-  if (restart && !dead) {
-    // more active rows than register slots (or a degenerate Gram system):
-    // solve again with the general solver
-    const QPInfo r = qp_solve_lds<T, G>(sh, C, lane, i, N, on, px, py, uhx, uhy, lox, hix, loy,
-                                        hiy, ux, uy);
-    info.status = r.status;
-    info.iters += r.iters;
-    q = r.q;
-    out.in_lds = 1;
-  } else {
-    out.in_lds = 0;
-    if (dead) {
-      info.status = 1;
-      q = 0;
-      if (on) {
-        ux = lox <= hix ? tmin(tmax(uhx, lox), hix) : T(0.5) * (lox + hix);
-        uy = loy <= hiy ? tmin(tmax(uhy, loy), hiy) : T(0.5) * (loy + hiy);
+  out.in_lds = 0;
+  if (dead) {
+    info.status = 1;
+    q = 0;
+    if (on) {
+      ux = lox <= hix ? tmin(tmax(uhx, lox), hix) : T(0.5) * (lox + hix);
+      uy = loy <= hiy ? tmin(tmax(uhy, loy), hiy) : T(0.5) * (loy + hiy);
+    }
+  } else if (restart) {
+    // more active rows than register slots: the general solver carries on
+    // from this active set; a degenerate Gram system: it starts from the clip
+    typedef __attribute__((address_space(3))) T LdsT;
+    out.in_lds = carry ? 2 : 1;
+    LdsT *hv = handover<T, G>(sh) + i;
+    const T v[kHandover - 2] = {uhx, uhy, lox, hix, loy, hiy, T(fx), T(fy), mux, muy};
+#pragma unroll
+    for (int c = 2; c < kHandover; ++c) hv[c * G] = v[c - 2];
+    if constexpr (G > 2) {
+      if (carry) {
+#pragma unroll
+        for (int a = 0; a < kQR; ++a)
+          if (i == sb[a])
+            sh->row[a] = (typename QPRow<T>::vec){T(sa[a] | sb[a] << 8), ccx[a], ccy[a], slam[a]};
+        if (i == pb) {
+          sh->row[kQR] = (typename QPRow<T>::vec){T(pa | pb << 8), cpx, cpy, bp};
+          *(LdsT *)(sh->row + kQR + 1) = lam_p;
+        }
       }
     }
+    wave_lds_fence();
   }
   out.ux = ux;
   out.uy = uy;
@@ -956,13 +1182,18 @@ __device__ __noinline__ QPLoopOut<T> qp_active_set(QPScratch<T, G> *sh, int lane
 #pragma unroll
       for (int a = 0; a < kQR; ++a) {
         if (a < q) {
-          sh->act[a] = sa[a] | (sb[a] << 8);
+          sh->row[a].x = T(sa[a] | (sb[a] << 8));
           sh->lam[a] = slam[a];
         }
       }
     }
     wave_lds_fence();
   }
+  if (__ballot(out.in_lds != 0) != 0)  // wavefront-uniform: a tail call
+    [[clang::musttail]] return qp_general<T, G>(
+        sh, lane, out.in_lds | out.status << 8 | out.q << 16, N, true, T(0), T(0), out.ux, out.uy,
+        T(0), T(0), T(0), T(0), false, out.iters, 0, T(0), T(0), T(0), rs2, gamma, vmax4, tol_add,
+        eps_z, eps_r, qp_cap, false);
   __builtin_amdgcn_s_setprio(0);
   return out;
 }
@@ -1465,9 +1696,9 @@ __device__ QPInfo qp_solve(QPScratch<T, G> *sh, ConstRef<T> K, int qp_cap, int l
           rdx = flipr ? -rdx : rdx;
           rdy = flipr ? -rdy : rdy;
           // a seeded loop starts at this guess, where r is the most violated
-          // row: handed over through the group's scratch (L[0..3])
+          // row: handed over through the group's scratch (H[0..3])
           if (seeded && i == 0)
-            reinterpret_cast<float4 *>(sh->L)[0] = make_float4(__int_as_float(rid), rdx, rdy, rbb);
+            *reinterpret_cast<floatx4 *>(sh->H) = (floatx4){__int_as_float(rid), rdx, rdy, rbb};
           const int ra = rid >> 4, rb = rid & 15;
           const bool try2 =
               seeded && rid >= 0 && (ra == pa || ra == pb || rb == pa || rb == pb);
@@ -1570,7 +1801,7 @@ __device__ QPInfo qp_solve(QPScratch<T, G> *sh, ConstRef<T> K, int qp_cap, int l
   }
 
   if (__builtin_expect(run_gi, 0)) {
-    const QPLoopOut<T> r = qp_active_set<T, G>(sh, lane, i, N, on, px, py, uhx, uhy, lox, hix,
+    const QPLoopOut<T> r = qp_active_set<T, G>((LdsScratch<T, G> *)sh, lane, i, N, on, px, py, uhx, uhy, lox, hix,
                                                loy, hiy, seed, fpa, fpb, fl1, fdx, fdy, C.rs2,
                                                C.gamma, C.vmax4, C.tol_add, C.eps_z, C.eps_r,
                                                qp_cap, act_out != nullptr);

@@ -30,7 +30,6 @@ namespace rs {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef short shortx2 __attribute__((ext_vector_type(2)));
 
 constexpr int kRollBlock = 256;
