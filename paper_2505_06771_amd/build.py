@@ -36,6 +36,7 @@ HIPCC_FLAGS = [
 # launches by about 1% in same-box comparisons; on env_run it does not help).
 FILE_FLAGS = {
     "rs_rollout.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+    "rs_rollout_split.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
 }
 # the host pass does not know the packed-fp32 feature; that warning is noise
 _NOISE = ("packed-fp32-ops",)

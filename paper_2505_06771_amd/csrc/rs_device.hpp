@@ -252,7 +252,7 @@ struct PhaseClock {
 };
 
 // Compile-time loop: f(std::integral_constant<int, K>) for K in [B, E).
-template <int B, int E, typename F> __device__ __forceinline__ void static_for(F &&f) {
+template <int B, int E, typename F> __host__ __device__ __forceinline__ void static_for(F &&f) {
   if constexpr (B < E) {
     f(std::integral_constant<int, B>{});
     static_for<B + 1, E>(f);
@@ -294,6 +294,41 @@ template <typename T> struct ConstRef {
     asm volatile("" : "+s"(a));  // opaque: the load stays at the use
     return (const __attribute__((address_space(4))) SimConst<T> *)a;
   }
+  __device__ __forceinline__ ConstRef<T> cold() const { return *this; }
+};
+// The constants of a step in vector registers, loaded once before a step loop.
+// For loops that run one wavefront per SIMD: nothing covers a scalar load's
+// latency there, and there are vector registers to spare.
+template <typename T> struct ConstReg {
+  SimConst<T> C;
+  ConstRef<T> ref;
+  __device__ __forceinline__ explicit ConstReg(ConstRef<T> r) : ref(r) {
+    const auto *P = r.get();
+    auto pin = [](T &dst, T v) {
+      asm volatile("" : "+v"(v));
+      dst = v;
+    };
+    pin(C.xwl, P->xwl); pin(C.xwh, P->xwh); pin(C.ywl, P->ywl); pin(C.ywh, P->ywh);
+    pin(C.dt, P->dt); pin(C.l, P->l); pin(C.inv_l, P->inv_l);
+    pin(C.gamma, P->gamma); pin(C.rs2, P->rs2); pin(C.kb, P->kb);
+    pin(C.vmax, P->vmax); pin(C.vmax4, P->vmax4); pin(C.aspeed, P->aspeed); pin(C.kp, P->kp);
+    pin(C.wstep, P->wstep); pin(C.kv, P->kv); pin(C.kw, P->kw);
+    pin(C.krho, P->krho); pin(C.kalpha, P->kalpha);
+    pin(C.prey_step, P->prey_step); pin(C.tag_r, P->tag_r); pin(C.tag_reward, P->tag_reward);
+    pin(C.halfL, P->halfL); pin(C.wheel_lim, P->wheel_lim);
+    pin(C.inv_R, P->inv_R); pin(C.R_over_L, P->R_over_L);
+    pin(C.tol_add, P->tol_add); pin(C.eps_z, P->eps_z); pin(C.eps_r, P->eps_r);
+    // wavefront-uniform decisions stay scalar
+    C.R = P->R;
+    C.noise = P->noise;
+    C.goal_r = P->goal_r;
+    C.max_steps = P->max_steps;
+    C.controller = P->controller;
+    C.key0 = P->key0;
+    C.key1 = P->key1;
+  }
+  __device__ __forceinline__ const SimConst<T> *get() const { return &C; }
+  __device__ __forceinline__ ConstRef<T> cold() const { return ref; }
 };
 // `offset` = offsetof(kernel argument struct, its SimConst member); the
 // struct must be the kernel's first parameter.

@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kBlock) void k_env_steps(StepsArgs<T> A) {
   T x = A.x[r], y = A.y[r], th = A.th[r], gx = A.gx[r], gy = A.gy[r];
   int step = A.step[e], episode = A.episode[e];
   const uint32_t env_id = A.env_base + (uint32_t)e;
-  const ConstRef<T> K = kernarg_const<T>(offsetof(StepsArgs<T>, C));
+  const ConstReg<T> K(kernarg_const<T>(offsetof(StepsArgs<T>, C)));
   // complete the state loads before the loop: an in-loop wait on them would
   // also wait for the loop's own stores
   __builtin_amdgcn_s_waitcnt(0);

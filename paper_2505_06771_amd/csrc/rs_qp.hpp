@@ -83,6 +83,8 @@ __device__ __forceinline__ float tmax(float a, float b) { return __builtin_fmaxf
 __device__ __forceinline__ float tmin(float a, float b) { return __builtin_fminf(a, b); }
 __device__ __forceinline__ double tmax(double a, double b) { return __builtin_fmax(a, b); }
 __device__ __forceinline__ double tmin(double a, double b) { return __builtin_fmin(a, b); }
+__device__ __forceinline__ float tfma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double tfma(double a, double b, double c) { return __builtin_fma(a, b, c); }
 // clamp to [lo, hi] with lo <= hi: one median-of-three in FP32
 __device__ __forceinline__ float tclamp(float x, float lo, float hi) {
   return __builtin_amdgcn_fmed3f(x, lo, hi);
@@ -1198,8 +1200,8 @@ __device__ __noinline__ QPLoopOut<T> qp_active_set(LdsScratch<T, G> *sh, int lan
   return out;
 }
 
-template <typename T, int G>
-__device__ QPInfo qp_solve(QPScratch<T, G> *sh, ConstRef<T> K, int qp_cap, int lane, int i, int N,
+template <typename T, int G, typename KT>
+__device__ __forceinline__ QPInfo qp_solve(QPScratch<T, G> *sh, const KT &K, int qp_cap, int lane, int i, int N,
                            bool on, T px, T py, T uhx, T uhy, T lox, T hix, T loy, T hiy, T &ux,
                            T &uy, QPActive<T> *act_out = nullptr) {
   const auto &C = *K.get();  // the solver's constants, loaded for this phase

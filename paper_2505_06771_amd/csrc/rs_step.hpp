@@ -32,11 +32,14 @@ __device__ __forceinline__ void preclip(const CS &C, T &ux, T &uy) {
 }
 
 // Single-integrator command at the projection point -> unicycle (v, w), then
-// GRITSBot wheel-speed saturation.
-template <typename T, typename CS>
+// GRITSBot wheel-speed saturation. Where two products are summed the one that
+// is rounded on its own is written out (here and in prey_move): left to the
+// compiler it depends on what else a kernel does with the products, and the
+// kernels of a scenario have to give the same trajectory.
+template <bool PP, typename T, typename CS>
 __device__ __forceinline__ void si_to_uni(const CS &C, T c, T s, T ux, T uy, T &v, T &w) {
-  v = c * ux + s * uy;
-  w = (c * uy - s * ux) * C.inv_l;
+  v = PP ? tfma(c, ux, s * uy) : tfma(s, uy, c * ux);
+  w = tfma(c, uy, -(s * ux)) * C.inv_l;
   if (C.R > T(0)) {
     T phr = (v + C.halfL * w) * C.inv_R;
     T phl = (v - C.halfL * w) * C.inv_R;
@@ -146,16 +149,27 @@ __device__ __forceinline__ void prey_move(const CS &C, QPScratch<T, G> *sh, int 
   constexpr double dir_s[16] = {0, kS, kH, kC, 1, kC, kH, kS, 0, -kS, -kH, -kC, -1, -kC, -kH, -kS};
   const T far = T(1e30);
   const T st = C.prey_step;
-  // candidate k's position (the same arithmetic wherever it is formed)
+  // candidate k's position (the same arithmetic wherever it is formed: the
+  // products are constant over a step loop, and hoisted out of it they would
+  // be rounded)
   auto cand = [&](auto kc, T &cx, T &cy) {
     constexpr int k = decltype(kc)::value;
     if constexpr (k == 0) {
       cx = qx;
       cy = qy;
     } else {
-      cx = tclamp(qx + st * T(dir_c[k - 1]), C.xwl, C.xwh);
-      cy = tclamp(qy + st * T(dir_s[k - 1]), C.ywl, C.ywh);
+      cx = tclamp(tfma(st, T(dir_c[k - 1]), qx), C.xwl, C.xwh);
+      cy = tclamp(tfma(st, T(dir_s[k - 1]), qy), C.ywl, C.ywh);
     }
+  };
+  // squared distance to candidate k, the order of its rounding written out:
+  // the arg-max decides between scores that may be equal but for it, so every
+  // kernel has to round them alike
+  auto score = [&](auto kc, T ex, T ey) {
+    constexpr int k = decltype(kc)::value;
+    constexpr int q = k == 0 ? 0 : k - 1;
+    constexpr bool xfirst = k == 0 || (G == 2 ? dir_c[q] != 0 : dir_s[q] == 0);
+    return xfirst ? tfma(ex, ex, ey * ey) : tfma(ey, ey, ex * ex);
   };
   if constexpr (G == 2 || sizeof(QPScratch<T, G>) < sizeof(T) * NCAND * G) {
     T best = T(-1), bx = qx, by = qy;
@@ -164,7 +178,7 @@ __device__ __forceinline__ void prey_move(const CS &C, QPScratch<T, G> *sh, int 
       T cx, cy;
       cand(kc, cx, cy);
       const T ex = cx - x, ey = cy - y;
-      const T sc = gmin<G>(on ? ex * ex + ey * ey : far);
+      const T sc = gmin<G>(on ? score(kc, ex, ey) : far);
       const bool bt = sc > best;
       best = bt ? sc : best;
       bx = bt ? cx : bx;
@@ -179,7 +193,7 @@ __device__ __forceinline__ void prey_move(const CS &C, QPScratch<T, G> *sh, int 
       T cx, cy;
       cand(kc, cx, cy);
       const T ex = cx - x, ey = cy - y;
-      d[k * G + i] = on ? ex * ex + ey * ey : far;
+      d[k * G + i] = on ? score(kc, ex, ey) : far;
     });
     wave_lds_fence();
     T best = T(-1);
@@ -214,8 +228,8 @@ __device__ __forceinline__ void prey_move(const CS &C, QPScratch<T, G> *sh, int 
       ds = bk == k ? T(dir_s[k - 1]) : ds;
     });
     if (bk > 0) {
-      qx = tclamp(qx + st * dc, C.xwl, C.xwh);
-      qy = tclamp(qy + st * ds, C.ywl, C.ywh);
+      qx = tclamp(tfma(st, dc, qx), C.xwl, C.xwh);
+      qy = tclamp(tfma(st, ds, qy), C.ywl, C.ywh);
     }
   }
 }
@@ -286,8 +300,8 @@ template <typename T> struct StepOut {
 // the step (keys the action noise). `step`/`episode` are group-uniform and
 // updated. Observation of the post-step state is left to the caller (c, s
 // are refreshed).
-template <typename T, int G, bool PP = false>
-__device__ StepOut<T> env_step_group(ConstRef<T> K, int qp_cap, QPScratch<T, G> *sh, int lane,
+template <typename T, int G, bool PP, typename KT>
+__device__ __forceinline__ StepOut<T> env_step_group(const KT &K, int qp_cap, QPScratch<T, G> *sh, int lane,
                                      int i, int N, bool on, uint32_t env_id, uint32_t t, int action,
                                      T &x, T &y, T &th, T &c, T &s, T &gx, T &gy, int &step,
                                      int &episode, bool want_viol, PhaseClock *pc = nullptr) {
@@ -368,7 +382,7 @@ __device__ StepOut<T> env_step_group(ConstRef<T> K, int qp_cap, QPScratch<T, G> 
                                                 loy, hiy)
                           : T(0);
   T v, w;
-  si_to_uni(*K.get(), c, s, ux, uy, v, w);
+  si_to_uni<PP>(*K.get(), c, s, ux, uy, v, w);
   if (on) integrate(*K.get(), c, s, v, w, x, y, th);
   // reward and termination
   step += 1;
@@ -399,7 +413,7 @@ __device__ StepOut<T> env_step_group(ConstRef<T> K, int qp_cap, QPScratch<T, G> 
     episode += 1;
     step = 0;
     T nx, ny, nth, ngx, ngy;
-    reset_env<T, G, PP>(K, env_id, (uint32_t)episode, i, N, lane, nx, ny, nth, ngx, ngy);
+    reset_env<T, G, PP>(K.cold(), env_id, (uint32_t)episode, i, N, lane, nx, ny, nth, ngx, ngy);
     if (on) { x = nx; y = ny; th = nth; gx = ngx; gy = ngy; }
   }
   sincos_t(th, &s, &c);
