@@ -352,9 +352,10 @@ typedef struct {
   int32_t lanes_per_env[17]; /* indexed by N: power of two >= N, <= 16; 0 = smallest */
   int32_t qp_iters[17];      /* indexed by N: active-set iteration cap; 0 = 8N+32 */
   int32_t envs_per_wave[17]; /* indexed by N: envs sharing a wavefront, 1..64/lanes;
-                                0 = 64/lanes (a wavefront runs the solver stages any
-                                of its envs needs, so fewer envs per wavefront run
-                                fewer of them per env, on more wavefronts) */
+                                0 = 64/lanes, fewer while SIMDs are idle (a wavefront
+                                runs the solver stages any of its envs needs, so fewer
+                                envs per wavefront run fewer of them per env, on more
+                                wavefronts) */
 } rs_schedule;
 
 rs_status rs_plan_create(rs_ctx *ctx, int32_t num_envs, const int32_t *robots_per_env,

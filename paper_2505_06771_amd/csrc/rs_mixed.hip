@@ -32,9 +32,14 @@ __device__ __forceinline__ void run_tile(const RunArgs &A, ConstRef<float> K, ch
                                          int lane, int first, int count) {
   QPScratch<float, G> *sh = reinterpret_cast<QPScratch<float, G> *>(wave_lds) + lane / G;
   const int i = lane & (G - 1);
+  // Lane groups past the tile's envs run one of them again, without storing:
+  // a wavefront with under 16 active lanes loses issue slots to the other
+  // wavefronts of its CU on this hardware (1024 wavefronts of one env each:
+  // 4 robots 2.65 us a step with the other lanes off, 1.33 us with them
+  // running along, 8 robots 3.55 and 1.80 us).
   const int grp = lane / G;
-  if (grp >= count) return;  // whole group
-  const int e = A.items[first + grp];
+  const bool own = grp < count;
+  const int e = A.items[first + grp % count];
   const int N = A.nrob[e];
   const bool on = i < N;
   const size_t r = (size_t)A.offset[e] + (on ? i : 0);
@@ -47,7 +52,7 @@ __device__ __forceinline__ void run_tile(const RunArgs &A, ConstRef<float> K, ch
   if (A.reset_all || (A.reset_only && A.reset_only[e]) || consume) {
     reset_env<float, G, PP>(K, env_id, (uint32_t)episode, i, N, lane, x, y, th, gx, gy);
     step = 0;
-    if (consume && i == 0) A.reset_mask[e] = 0;
+    if (consume && own && i == 0) A.reset_mask[e] = 0;
   } else if (on) {
     x = A.x[r]; y = A.y[r]; th = A.th[r]; gx = A.gx[r]; gy = A.gy[r];
   }
@@ -67,13 +72,14 @@ __device__ __forceinline__ void run_tile(const RunArgs &A, ConstRef<float> K, ch
                                                        (uint32_t)(tb + k), action, x, y, th, c, s, gx, gy, step,
                                                        episode, false);
     rsum += so.reward;
-    if (i == 0) {
+    if (own && i == 0) {
       if (A.reward_out) A.reward_out[(size_t)k * A.E + e] = so.reward;
       if (A.done_out) A.done_out[(size_t)k * A.E + e] = so.done ? 1 : 0;
       if (A.qp_stats) qp_stats_add(A.qp_stats + (size_t)e * kQPStats, so.qp);
       qp_fail_count(A.qp_fail, so.qp);
     }
   }
+  if (!own) return;
   if (on) { A.x[r] = x; A.y[r] = y; A.th[r] = th; A.gx[r] = gx; A.gy[r] = gy; }
   if (A.obs_final)
     write_obs<float, G>(A.obs_final + A.obs_off[e] + (size_t)(on ? i : 0) * (2 * N + 4), lane, i,
@@ -126,19 +132,20 @@ int lanes_for(const rs_schedule &sched, int n) {
   return pow2_group(n);
 }
 
-int envs_per_wave_for(const rs_schedule &sched, int n) {
-  const int full = 64 / lanes_for(sched, n);
-  const int c = sched.envs_per_wave[n];
-  return (c >= 1 && c <= full) ? c : full;
-}
-
 void build_tiles(const std::vector<int32_t> &envs, const std::vector<int32_t> &nrob_of,
-                 const rs_schedule &sched, std::vector<int32_t> &tiles,
+                 const rs_schedule &sched, int simds, std::vector<int32_t> &tiles,
                  std::vector<int32_t> &items) {
+  int32_t total[RS_MAX_ROBOTS + 1] = {}, lanes[RS_MAX_ROBOTS + 1] = {}, epw[RS_MAX_ROBOTS + 1] = {};
+  for (int32_t e : envs) ++total[nrob_of[e]];
+  for (int n = 2; n <= RS_MAX_ROBOTS; ++n) {
+    lanes[n] = lanes_for(sched, n);
+    epw[n] = scheduled_envs_per_wave(sched, n);
+  }
+  spread_envs(total, lanes, simds, epw);
   // tiles hold envs of one (lanes, envs-per-wavefront) class, by robot count
   auto cls = [&](int32_t e) {
     const int n = nrob_of[e];
-    return lanes_for(sched, n) * 128 + envs_per_wave_for(sched, n);
+    return lanes[n] * 128 + epw[n];
   };
   std::vector<int32_t> order(envs);
   std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
@@ -151,8 +158,8 @@ void build_tiles(const std::vector<int32_t> &envs, const std::vector<int32_t> &n
   size_t k = 0;
   while (k < order.size()) {
     const int c0 = cls(order[k]);
-    const int g = lanes_for(sched, nrob_of[order[k]]);
-    const int cap = envs_per_wave_for(sched, nrob_of[order[k]]);
+    const int g = lanes[nrob_of[order[k]]];
+    const int cap = epw[nrob_of[order[k]]];
     const int first = (int)items.size();
     int count = 0;
     while (k < order.size() && count < cap && cls(order[k]) == c0) {
@@ -176,7 +183,7 @@ static rs_status plan_upload(rs_plan *pl) {
   std::vector<int32_t> envs(pl->num_envs);
   std::iota(envs.begin(), envs.end(), 0);
   std::vector<int32_t> tiles, items;
-  build_tiles(envs, pl->robots_host, pl->sched, tiles, items);
+  build_tiles(envs, pl->robots_host, pl->sched, 4 * pl->ctx->num_cus, tiles, items);
   pl->num_tiles = (int32_t)(tiles.size() / 4);
   if (pl->tiles_dev) (void)hipFree(pl->tiles_dev);
   if (pl->items_dev) (void)hipFree(pl->items_dev);
@@ -588,9 +595,16 @@ static rs_status autotune_impl(rs_ctx *ctx, const rs_params *p, const std::vecto
         }
       }
       // report the effective values for the tuned sizes
+      int32_t total[RS_MAX_ROBOTS + 1] = {}, lanes[RS_MAX_ROBOTS + 1] = {}, epw[RS_MAX_ROBOTS + 1] = {};
+      for (int32_t n : counts) ++total[n];
+      for (int n = 2; n <= RS_MAX_ROBOTS; ++n) {
+        lanes[n] = lanes_for(best, n);
+        epw[n] = scheduled_envs_per_wave(best, n);
+      }
+      spread_envs(total, lanes, 4 * ctx->num_cus, epw);
       for (int32_t n : sizes) {
-        best.lanes_per_env[n] = lanes_for(best, n);
-        best.envs_per_wave[n] = envs_per_wave_for(best, n);
+        best.lanes_per_env[n] = lanes[n];
+        best.envs_per_wave[n] = epw[n];
         if (best.qp_iters[n] <= 0) best.qp_iters[n] = 8 * n + 32;
       }
       ctx->sched = best;

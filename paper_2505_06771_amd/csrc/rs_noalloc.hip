@@ -47,7 +47,8 @@ struct PlanArgs {
   unsigned char *s;     // this device's array
   int E;
   int32_t lanes[RS_MAX_ROBOTS + 1];  // lanes per env, by robot count
-  int32_t epw[RS_MAX_ROBOTS + 1];    // envs per wavefront tile, by robot count
+  int32_t epw[RS_MAX_ROBOTS + 1];    // envs per wavefront tile, by robot count (0: by the counts)
+  int simds;
 };
 
 template <typename T> __device__ T wave_incl_scan(T v, int lane) {
@@ -76,7 +77,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_noalloc_plan(PlanArgs P) {
   __shared__ int32_t w_cnt[kPlanWaves][RS_MAX_ROBOTS + 1];  // per count, then start position
   __shared__ int32_t w_bad[kPlanWaves];
   __shared__ int32_t total[RS_MAX_ROBOTS + 1], item_base[RS_MAX_ROBOTS + 1],
-      tile_base[RS_MAX_ROBOTS + 1];
+      tile_base[RS_MAX_ROBOTS + 1], epw[RS_MAX_ROBOTS + 1];
   __shared__ int32_t bad;
   int32_t *hdr = reinterpret_cast<int32_t *>(P.s + kHdr);
   int32_t *offset = reinterpret_cast<int32_t *>(P.s + kOffset);
@@ -148,9 +149,13 @@ __global__ __launch_bounds__(kPlanThreads) void k_noalloc_plan(PlanArgs P) {
         }
         total[m] = c;
         item_base[m] = ib;
-        tile_base[m] = tb;
+        epw[m] = P.epw[m];
         ib += c;
-        tb += (c + P.epw[m] - 1) / P.epw[m];
+      }
+      spread_envs(total, P.lanes, P.simds, epw);
+      for (int m = 2; m <= RS_MAX_ROBOTS; ++m) {
+        tile_base[m] = tb;
+        tb += (total[m] + epw[m] - 1) / epw[m];
       }
       hdr[0] = tb;
       hdr[1] = 0;
@@ -189,7 +194,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_noalloc_plan(PlanArgs P) {
 
   // tiles, count after count
   for (int m = 2; m <= RS_MAX_ROBOTS; ++m) {
-    const int c = total[m], cap = P.epw[m];
+    const int c = total[m], cap = epw[m];
     const int nt = (c + cap - 1) / cap;
     for (int k = threadIdx.x; k < nt; k += kPlanThreads)
       tiles[tile_base[m] + k] = make_int4(P.lanes[m], item_base[m] + k * cap, min(cap, c - k * cap), 0);
@@ -254,11 +259,12 @@ rs_status env_run_noalloc(rs_ctx *ctx, const rs_params *p, const int32_t *robots
   P.bad_out = bad_envs;
   P.s = sc;
   P.E = E;
-  int epw_min = 64;
+  P.simds = 4 * ctx->num_cus;
+  int epw_min = 64;  // of the counts' widest tiles
   for (int n = 2; n <= RS_MAX_ROBOTS; ++n) {
     P.lanes[n] = lanes_for(sched, n);
-    P.epw[n] = envs_per_wave_for(sched, n);
-    epw_min = std::min(epw_min, (int)P.epw[n]);
+    P.epw[n] = scheduled_envs_per_wave(sched, n);
+    epw_min = std::min(epw_min, P.epw[n] ? (int)P.epw[n] : 64 / (int)P.lanes[n]);
   }
   const hipStream_t st = (hipStream_t)stream;
   hipLaunchKernelGGL(k_noalloc_plan, dim3(1), dim3(kPlanThreads), 0, st, P);
@@ -272,9 +278,10 @@ rs_status env_run_noalloc(rs_ctx *ctx, const rs_params *p, const int32_t *robots
   std::memset(&A, 0, sizeof(A));
   A.C = make_const<float>(*p);
   A.E = E;
-  // grid for the most tiles any counts can need; the kernel reads the real
+  // grid for the most tiles any counts can need (narrower ones are only made
+  // up to one per SIMD, and never more than envs); the kernel reads the real
   // number from the work list
-  A.num_tiles = (E + epw_min - 1) / epw_min + (RS_MAX_ROBOTS - 1);
+  A.num_tiles = std::max((E + epw_min - 1) / epw_min + (RS_MAX_ROBOTS - 1), std::min(E, P.simds));
   A.num_tiles_dev = reinterpret_cast<const int32_t *>(sc + kHdr);
   A.env_base = (uint32_t)b->env_id_base;
   A.tiles = reinterpret_cast<const int4 *>(sc + kTiles);

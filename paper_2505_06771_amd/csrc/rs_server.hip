@@ -248,7 +248,7 @@ static rs_status launch_tick(rs_server *s) {
     return RS_ERR_DEVICE;
   }
   std::vector<int32_t> tiles, items;
-  build_tiles(envs, s->nrob_of, s->ctx->sched, tiles, items);
+  build_tiles(envs, s->nrob_of, s->ctx->sched, 4 * s->ctx->num_cus, tiles, items);
   const int k = s->cur;
   s->cur ^= 1;
   RS_CHECK_HIP(hipEventSynchronize(s->staging_free[k]));
