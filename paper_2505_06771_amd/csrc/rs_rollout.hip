@@ -81,16 +81,15 @@ extern "C" rs_status rollout(rs_ctx *ctx, const rs_params *p, const rs_batch *b,
   const int G = pow2_group(A.N);
   // Envs per wavefront. A step is one long dependency chain, and a wavefront
   // runs the solver stages that any of its envs needs, so while SIMDs are idle
-  // fewer envs per wavefront make a shorter step: 4.5 -> 2.5 us at 96 x 6
-  // (12 -> 48 wavefronts), 3.9 -> 3.0 us at 2048 x 8 (256 -> 1024). Below one
-  // 16-row MLP tile nothing more is saved (2.6 us at two envs of 8, 2.8-3.1 at
-  // one), above 32 lanes the tiles of the split kernel run one after the
-  // other, and with two wavefronts per SIMD full ones win (4.1 against 5.5 us
-  // at 4096 x 8 with 512 and 2048 wavefronts).
+  // fewer envs per wavefront make a shorter step: 4.5 -> 2.3 us at 96 x 6 (12
+  // -> 96 wavefronts), 3.9 -> 3.0 us at 2048 x 8 (256 -> 1024). Above 32 lanes
+  // the tiles of the split kernel run one after the other, and with two
+  // wavefronts per SIMD full ones win (4.1 against 5.5 us at 4096 x 8 with 512
+  // and 2048 wavefronts).
   const int full = 64 / G, simds = 4 * ctx->num_cus;
   A.epw = full;
   if (!qp_stats)
-    for (int n = std::max(1, 16 / G); n * G <= 32 && A.epw == full; n *= 2)
+    for (int n = 1; n * G <= 32 && A.epw == full; n *= 2)
       if ((A.E + n - 1) / n <= simds) A.epw = n;
   const int waves = (A.E + A.epw - 1) / A.epw;
   const dim3 grid((waves + kRollWaves - 1) / kRollWaves);

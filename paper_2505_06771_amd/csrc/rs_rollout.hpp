@@ -182,14 +182,19 @@ __global__ __launch_bounds__(kRollBlock, (SPLIT ? 1 : rollout_waves_per_simd<G, 
   }
   __syncthreads();  // the only block-wide barrier, before any wavefront leaves
   const int i = lane & (G - 1);
-  const int grp = lane / G;
   const int e0 = (blockIdx.x * kRollWaves + wave) * EPW;
   if (e0 >= A.E) return;  // the whole wavefront leaves together
+  // SPLIT: lane groups past the wavefront's envs run one of them again without
+  // storing (a wavefront with under 16 active lanes loses issue slots to the
+  // others of its CU)
+  const int held = SPLIT ? min(EPW, A.E - e0) : 64 / G;
+  const int grp = SPLIT ? (lane / G) % held : lane / G;
+  const bool own = !SPLIT || lane / G < held;
   const int e = e0 + grp;
   constexpr int N = NC;
   typedef std::conditional_t<SPLIT, ConstReg<float>, ConstRef<float>> Consts;
   const Consts K(kernarg_const<float>(offsetof(RolloutArgs, C)));
-  const bool env_ok = e < A.E && (!SPLIT || grp < EPW);
+  const bool env_ok = e < A.E;
   const bool on = env_ok && i < N;
   // robot index (E * N < 2^31, checked by the entry point)
   const uint32_t r = on ? (uint32_t)(e * N + i) : 0u;
@@ -299,7 +304,7 @@ __global__ __launch_bounds__(kRollBlock, (SPLIT ? 1 : rollout_waves_per_simd<G, 
           }
           o8[q] = pack_bf16x8<false>(lo4, hi4);
         }
-        if (A.obs) {
+        if (A.obs && own) {
           float *dst = A.obs + ((size_t)t * A.E + e0) * (size_t)(NC * D);  // wavefront-uniform
           if constexpr (D % 4 == 0) {
             float4 *g4 = reinterpret_cast<float4 *>(dst) + row * (D / 4);
@@ -389,7 +394,8 @@ __global__ __launch_bounds__(kRollBlock, (SPLIT ? 1 : rollout_waves_per_simd<G, 
 
     pc.mark(kPhMlp);
     // ---- 3. categorical draw in the robot's own lane ----------------------
-    const float4 la = logit_w[lane], lb = logit_w[64 + lane];
+    const int col = SPLIT ? grp * G + i : lane;  // my robot's MLP column
+    const float4 la = logit_w[col], lb = logit_w[64 + col];
     const float l5[5] = {la.x, la.y, la.z, la.w, lb.x};
     float mx = l5[0];
 #pragma unroll
@@ -438,7 +444,7 @@ __global__ __launch_bounds__(kRollBlock, (SPLIT ? 1 : rollout_waves_per_simd<G, 
     }
     // per-step base pointers are uniform; the lane offsets are 32-bit
     uint8_t *act_t = A.actions + (size_t)t * (size_t)A.E * (size_t)N;
-    if (on) act_t[r] = (uint8_t)action;
+    if (on && own) act_t[r] = (uint8_t)action;
 
     pc.mark(kPhSample);
     // ---- 4. env step --------------------------------------------------------
@@ -452,7 +458,7 @@ __global__ __launch_bounds__(kRollBlock, (SPLIT ? 1 : rollout_waves_per_simd<G, 
                                                          nullptr
 #endif
                                                          );
-      if (il == 0) {
+      if (il == 0 && own) {
         (A.reward + (size_t)t * A.E)[(uint32_t)e] = so.reward;
         (A.done + (size_t)t * A.E)[(uint32_t)e] = so.done ? 1 : 0;
         if constexpr (STATS) qp_stats_add(A.qp_stats + (size_t)e * kQPStats, so.qp);
@@ -460,8 +466,8 @@ __global__ __launch_bounds__(kRollBlock, (SPLIT ? 1 : rollout_waves_per_simd<G, 
       }
     }
   }
-  if (on) { A.x[r] = x; A.y[r] = y; A.th[r] = th; A.gx[r] = gx; A.gy[r] = gy; }
-  if (env_ok && i == 0) { A.step[e] = step; A.episode[e] = episode; }
+  if (on && own) { A.x[r] = x; A.y[r] = y; A.th[r] = th; A.gx[r] = gx; A.gy[r] = gy; }
+  if (env_ok && own && i == 0) { A.step[e] = step; A.episode[e] = episode; }
 #ifdef RS_PHASE_TIMERS
   pc.add(kPhTotal, pc.last - t_begin);
   wave_lds_sync();

@@ -46,8 +46,9 @@ def test_split_wavefronts_match_full_ones(n, prey):
     pol = R.Policy(bf(w["w1"]), fl(w["b1"]), bf(w["w2"]), fl(w["b2"]), bf(w["w3"]), fl(w["b3"]))
     lanes = 2 if n == 2 else 4 if n <= 4 else 8 if n <= 8 else 16
     tile = max(1, 16 // lanes)
-    # one env, a partial wavefront, and past 1024 wavefronts of one tile (two tiles each)
-    for E in (1, 5 * tile + 1) + ((1024 * tile + 3,) if lanes < 16 else (1031,)):
+    # one env, several, then several per wavefront with a partial last one: one
+    # MLP tile, and two
+    for E in (1, 7, 1024 * max(tile // 2, 1) + 3, 1024 * tile + 3):
         banner(f"split rollout n={n} E={E} prey={prey}")
         got = _run(R, ctx, p, n, E, 20, pol, False)
         ref = _run(R, ctx, p, n, E, 20, pol, True)
