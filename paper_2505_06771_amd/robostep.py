@@ -183,7 +183,9 @@ def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
 
-        return torch.cuda.current_stream().cuda_stream
+        # the handle of torch.cuda.current_stream() without the Stream object
+        # around it: 0.3 us of a call's 6 instead of 2.9 of 9
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
