@@ -1,7 +1,7 @@
 // rs_lib.hip -- kernels and C-ABI entry points of the uniform-batch calls:
 // env_reset, env_step, barrier_certificate (FP32 and FP64).
 //
-// Launch shape: 256-thread blocks; each block holds 256/G environments, one
+// Launch shape: one wavefront per block, up to 64/G environments in it, one
 // aligned group of G = next power of two >= N lanes per environment, lane i
 // = robot i. State is structure-of-arrays in HBM (index e*N + i), so a group
 // reads N consecutive elements of each field and a wavefront reads 64/G*N
@@ -64,7 +64,31 @@ template <typename T> static bool aligned(const void *ptr) {
   return ((uintptr_t)ptr % sizeof(T)) == 0;
 }
 
-constexpr int kBlock = 256;
+// One wavefront per block: a block's LDS and slots are held until its slowest
+// wavefront ends, and a solve takes from 1 to 100 us (16384 envs x 16 robots,
+// one step: 211 us with four wavefronts per block, 185 us with one).
+constexpr int kBlock = 64;
+
+// Envs of a launch over its wavefronts, `epw` each (envs_per_wave): the env of
+// the calling lane's group and whether the group stores. Groups past the
+// wavefront's envs run one of them again: a wavefront with under 16 active
+// lanes loses issue slots to the others of its CU.
+template <int G> __device__ __forceinline__ int wave_env(int E, int epw, int lane, bool &own) {
+  const int e0 = blockIdx.x * epw, grp = lane / G;
+  const int held = min(epw, E - e0);
+  own = grp < held;
+  return e0 + (own ? grp : grp % held);
+}
+// Envs per wavefront: 64 / G, fewer while SIMDs are idle (a wavefront runs the
+// solver stages that any of its envs needs: one FP64 env of 4 robots, 1000
+// steps, 1.21 ms with the wavefront's other lanes off, 1.16 ms with them
+// running along; 4096 envs x 4, one step from a loop, 8.2 us in 256 wavefronts,
+// 8.0 us in 1024).
+static int envs_per_wave(int E, int G, int simds) {
+  int n = 1;
+  while (n < 64 / G && (E + n - 1) / n > simds) n *= 2;
+  return n;
+}
 static_assert(kQPStats == RS_QPS_COUNT, "qp_stats layout of robostep.h");
 
 // ---------------------------------------------------------------------------
@@ -72,7 +96,7 @@ static_assert(kQPStats == RS_QPS_COUNT, "qp_stats layout of robostep.h");
 // ---------------------------------------------------------------------------
 template <typename T> struct StepArgs {
   SimConst<T> C;
-  int E, N;
+  int E, N, epw;
   uint32_t env_base;
   uint32_t t_global;
   T *x, *y, *th, *gx, *gy;
@@ -90,8 +114,8 @@ __global__ __launch_bounds__(kBlock) void k_env_step(StepArgs<T> A) {
   __shared__ QPScratch<T, G> qs[kBlock / G];
   const int lane = threadIdx.x & 63;
   const int i = threadIdx.x & (G - 1);
-  const int e = blockIdx.x * (kBlock / G) + threadIdx.x / G;
-  if (e >= A.E) return;  // whole group leaves together
+  bool own;
+  const int e = wave_env<G>(A.E, A.epw, lane, own);
   const int N = A.N;
   const bool on = i < N;
   const size_t r = (size_t)e * N + (on ? i : 0);
@@ -108,6 +132,7 @@ __global__ __launch_bounds__(kBlock) void k_env_step(StepArgs<T> A) {
   StepOut<T> out = env_step_group<T, G, PP>(K, A.C.qp_cap, &qs[threadIdx.x / G], lane, i, N, on,
                                         env_id, (uint32_t)A.t_global, action, x, y, th, c, s, gx, gy, step, episode,
                                         A.maxviol != nullptr);
+  if (!own) return;
   if (on) {
     A.x[r] = x; A.y[r] = y; A.th[r] = th; A.gx[r] = gx; A.gy[r] = gy;
   }
@@ -130,7 +155,7 @@ __global__ __launch_bounds__(kBlock) void k_env_step(StepArgs<T> A) {
 // ---------------------------------------------------------------------------
 template <typename T> struct StepsArgs {
   SimConst<T> C;
-  int E, N, steps;
+  int E, N, epw, steps;
   uint32_t env_base;
   uint32_t t0;
   T *x, *y, *th, *gx, *gy;
@@ -147,8 +172,8 @@ __global__ __launch_bounds__(kBlock) void k_env_steps(StepsArgs<T> A) {
   __shared__ QPScratch<T, G> qs[kBlock / G];
   const int lane = threadIdx.x & 63;
   const int i = threadIdx.x & (G - 1);
-  const int e = blockIdx.x * (kBlock / G) + threadIdx.x / G;
-  if (e >= A.E) return;  // whole group leaves together
+  bool own;
+  const int e = wave_env<G>(A.E, A.epw, lane, own);
   const int N = A.N;
   const bool on = i < N;
   const size_t r = (size_t)e * N + (on ? i : 0);
@@ -169,13 +194,14 @@ __global__ __launch_bounds__(kBlock) void k_env_steps(StepsArgs<T> A) {
     const StepOut<T> out = env_step_group<T, G, PP>(K, A.C.qp_cap, &qs[threadIdx.x / G], lane, i,
                                                     N, on, env_id, t, action, x, y, th, c, s, gx,
                                                     gy, step, episode, false);
-    if (i == 0) {
+    if (own && i == 0) {
       if (A.reward) A.reward[(size_t)k * A.E + e] = out.reward;
       if (A.done) A.done[(size_t)k * A.E + e] = out.done ? 1 : 0;
       if (A.qp_stats) qp_stats_add(A.qp_stats + (size_t)e * kQPStats, out.qp);
       qp_fail_count(A.qp_fail, out.qp);
     }
   }
+  if (!own) return;
   if (on) {
     A.x[r] = x; A.y[r] = y; A.th[r] = th; A.gx[r] = gx; A.gy[r] = gy;
   }
@@ -229,7 +255,7 @@ __global__ __launch_bounds__(kBlock) void k_env_reset(ResetArgs<T> A) {
 // ---------------------------------------------------------------------------
 template <typename T> struct BarrierArgs {
   SimConst<T> C;
-  int E, N;
+  int E, N, epw;
   const T *px, *py, *uxn, *uyn;
   T *ux, *uy, *lambda;
   float *maxviol;
@@ -243,8 +269,8 @@ __global__ __launch_bounds__(kBlock) void k_barrier(BarrierArgs<T> A) {
   __shared__ QPScratch<T, G> qs[kBlock / G];
   const int lane = threadIdx.x & 63;
   const int i = threadIdx.x & (G - 1);
-  const int e = blockIdx.x * (kBlock / G) + threadIdx.x / G;
-  if (e >= A.E) return;
+  bool own;
+  const int e = wave_env<G>(A.E, A.epw, lane, own);
   const int N = A.N;
   const bool on = i < N;
   const size_t r = (size_t)e * N + (on ? i : 0);
@@ -259,6 +285,7 @@ __global__ __launch_bounds__(kBlock) void k_barrier(BarrierArgs<T> A) {
   QPActive<T> act;
   const QPInfo info = qp_solve<T, G>(sh, K, A.C.qp_cap, lane, i, N, on, px, py, unx, uny, lox,
                                      hix, loy, hiy, ux, uy, &act);
+  if (!own) return;
   if (on) { A.ux[r] = ux; A.uy[r] = uy; }
   if (A.lambda) {
     // each lane writes the pairs it owns (i, i+k mod N); active rows come
@@ -350,11 +377,12 @@ static rs_status do_env_step(rs_ctx *ctx, const rs_params *p, const rs_batch *b,
   A.qp_stats = qp_stats;
   A.qp_fail = ctx->qp_fail;
   const int G = pow2_group(A.N);
+  A.epw = envs_per_wave(A.E, G, 4 * ctx->num_cus);
   if (p->scenario == RS_SCN_PREDATOR_PREY) {
-    RS_DISPATCH_G(G, hipLaunchKernelGGL((k_env_step<T, GG, true>), dim3(blocks_for<T>(A.E, GG)),
+    RS_DISPATCH_G(G, hipLaunchKernelGGL((k_env_step<T, GG, true>), dim3((A.E + A.epw - 1) / A.epw),
                                         dim3(kBlock), 0, st, A));
   } else {
-    RS_DISPATCH_G(G, hipLaunchKernelGGL((k_env_step<T, GG, false>), dim3(blocks_for<T>(A.E, GG)),
+    RS_DISPATCH_G(G, hipLaunchKernelGGL((k_env_step<T, GG, false>), dim3((A.E + A.epw - 1) / A.epw),
                                         dim3(kBlock), 0, st, A));
   }
   return launch_status("env_step");
@@ -377,11 +405,12 @@ static rs_status do_env_steps(rs_ctx *ctx, const rs_params *p, const rs_batch *b
   A.qp_stats = qp_stats;
   A.qp_fail = ctx->qp_fail;
   const int G = pow2_group(A.N);
+  A.epw = envs_per_wave(A.E, G, 4 * ctx->num_cus);
   if (p->scenario == RS_SCN_PREDATOR_PREY) {
-    RS_DISPATCH_G(G, hipLaunchKernelGGL((k_env_steps<T, GG, true>), dim3(blocks_for<T>(A.E, GG)),
+    RS_DISPATCH_G(G, hipLaunchKernelGGL((k_env_steps<T, GG, true>), dim3((A.E + A.epw - 1) / A.epw),
                                         dim3(kBlock), 0, st, A));
   } else {
-    RS_DISPATCH_G(G, hipLaunchKernelGGL((k_env_steps<T, GG, false>), dim3(blocks_for<T>(A.E, GG)),
+    RS_DISPATCH_G(G, hipLaunchKernelGGL((k_env_steps<T, GG, false>), dim3((A.E + A.epw - 1) / A.epw),
                                         dim3(kBlock), 0, st, A));
   }
   return launch_status("env_steps");
@@ -426,7 +455,8 @@ static rs_status do_barrier(rs_ctx *ctx, const rs_params *p, int E, int N, const
   A.qp_stats = qp_stats;
   A.qp_fail = ctx->qp_fail;
   const int G = pow2_group(N);
-  RS_DISPATCH_G(G, hipLaunchKernelGGL((k_barrier<T, GG>), dim3(blocks_for<T>(E, GG)), dim3(kBlock),
+  A.epw = envs_per_wave(E, G, 4 * ctx->num_cus);
+  RS_DISPATCH_G(G, hipLaunchKernelGGL((k_barrier<T, GG>), dim3((E + A.epw - 1) / A.epw), dim3(kBlock),
                                       0, st, A));
   return launch_status("barrier_certificate");
 }
