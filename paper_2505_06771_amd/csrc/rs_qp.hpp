@@ -525,15 +525,20 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
 
   bool dead = false;
   bool settled = false;  // the command was formed from the rows since they last changed
-  if (!rebuild(q)) {
-    out = QPLoopOut<T>{ux, uy, 2, out.iters + iters0, 0, out.in_lds};
-    return;
-  }
+  // H has to be formed from the rows: at entry, and when a correction did not
+  // close the residual (again: it was formed for that). One place each for
+  // rebuild() and refine(): the solver is called from kernels that fill the
+  // instruction cache, and its size shows in their time.
+  bool stale = true, again = false;
   // the entering row: a pair (ra < rb, 2 D) or a bound
   bool pend = carry;
   int ra = (int)p.x & 255, rb = (int)p.x >> 8;
   T cx = p.y, cy = p.z, rhs = p.w;
   while (true) {
+    if (stale) {
+      if (!rebuild(q)) { out.status = 2; q = 0; break; }
+      stale = false;
+    }
     if (!pend) {
       // --- most violated row (normalised), its data as the argmax's payload ---
       T best = tol_add, bcx = T(0), bcy = T(0), bb = T(0);
@@ -576,10 +581,9 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
       gargmax_payload<G>(best, bid, bcx, bcy, bb);
       if (bid < 0) {
         if (settled) break;  // optimal
-        bool good = refine() <= tol_add;
-        if (!good) good = rebuild(q) && refine() <= T(8) * tol_add;
-        if (!good) { out.status = 2; break; }
-        settled = true;
+        settled = refine() <= (again ? T(8) * tol_add : tol_add);
+        if (!settled && again) { out.status = 2; break; }
+        stale = again = !settled;
         continue;
       }
       if (++out.iters > cap) { out.status = 2; break; }
@@ -624,7 +628,7 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
     for (int s = 0; s < S; ++s)
       if (i + s * G < q) lam[i + s * G] -= t * rk[s];
     lam_p += t;
-    settled = false;
+    settled = again = false;
     if (full) {
       grow(q, zz);
       if (i == 0) {
