@@ -142,35 +142,37 @@ void build_tiles(const std::vector<int32_t> &envs, const std::vector<int32_t> &n
     epw[n] = scheduled_envs_per_wave(sched, n);
   }
   spread_envs(total, lanes, simds, epw);
-  // tiles hold envs of one (lanes, envs-per-wavefront) class, by robot count
-  auto cls = [&](int32_t e) {
-    const int n = nrob_of[e];
-    return lanes[n] * 128 + epw[n];
-  };
-  std::vector<int32_t> order(envs);
-  std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-    const int ca = cls(a), cb = cls(b);
-    if (ca != cb) return ca < cb;
-    return nrob_of[a] < nrob_of[b];
+  // Longest steps first (wide groups, then few envs per wavefront, then many
+  // robots): a launch of more wavefronts than the SIMDs hold ends with its
+  // last tiles alone on the chip, and these should be the short ones. The
+  // mean tick of a served burst of 16 requests: 262 us with the shortest
+  // first, 221 us so. Tiles hold envs of one (lanes, envs-per-wavefront) class.
+  int ns[RS_MAX_ROBOTS - 1], kinds = 0;
+  for (int n = RS_MAX_ROBOTS; n >= 2; --n)
+    if (total[n]) ns[kinds++] = n;
+  std::stable_sort(ns, ns + kinds, [&](int a, int b) {
+    return lanes[a] != lanes[b] ? lanes[a] > lanes[b] : epw[a] < epw[b];
   });
+  int32_t at[RS_MAX_ROBOTS + 1], end = 0;
+  for (int k = 0; k < kinds; ++k) {
+    at[ns[k]] = end;
+    end += total[ns[k]];
+  }
+  items.resize(envs.size());
+  for (int32_t e : envs) items[at[nrob_of[e]]++] = e;
   tiles.clear();
-  items.clear();
-  size_t k = 0;
-  while (k < order.size()) {
-    const int c0 = cls(order[k]);
-    const int g = lanes[nrob_of[order[k]]];
-    const int cap = epw[nrob_of[order[k]]];
-    const int first = (int)items.size();
-    int count = 0;
-    while (k < order.size() && count < cap && cls(order[k]) == c0) {
-      items.push_back(order[k]);
-      ++k;
-      ++count;
+  int first = 0;
+  for (int k = 0; k < kinds;) {
+    const int g = lanes[ns[k]], cap = epw[ns[k]];
+    int stop = first;
+    for (; k < kinds && lanes[ns[k]] == g && epw[ns[k]] == cap; ++k) stop += total[ns[k]];
+    for (; first < stop; first += cap) {
+      tiles.push_back(g);
+      tiles.push_back(first);
+      tiles.push_back(std::min(cap, stop - first));
+      tiles.push_back(0);
     }
-    tiles.push_back(g);
-    tiles.push_back(first);
-    tiles.push_back(count);
-    tiles.push_back(0);
+    first = stop;
   }
 }
 
