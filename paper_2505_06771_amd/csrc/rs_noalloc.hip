@@ -279,9 +279,10 @@ rs_status env_run_noalloc(rs_ctx *ctx, const rs_params *p, const int32_t *robots
   A.C = make_const<float>(*p);
   A.E = E;
   // grid for the most tiles any counts can need (narrower ones are only made
-  // up to one per SIMD, and never more than envs); the kernel reads the real
+  // up to two per SIMD, and never more than envs); the kernel reads the real
   // number from the work list
-  A.num_tiles = std::max((E + epw_min - 1) / epw_min + (RS_MAX_ROBOTS - 1), std::min(E, P.simds));
+  A.num_tiles =
+      std::max((E + epw_min - 1) / epw_min + (RS_MAX_ROBOTS - 1), std::min(E, 2 * P.simds));
   A.num_tiles_dev = reinterpret_cast<const int32_t *>(sc + kHdr);
   A.env_base = (uint32_t)b->env_id_base;
   A.tiles = reinterpret_cast<const int4 *>(sc + kTiles);

@@ -56,13 +56,15 @@ int lanes_for(const rs_schedule &sched, int n);
 // Envs per wavefront tile for each robot count: the schedule's where it sets
 // one (epw[n] > 0), else 64 / lanes, and less while that leaves SIMDs idle. A
 // wavefront runs the solver stages that any of its envs needs, so fewer envs
-// make its steps shorter; beyond one wavefront per SIMD two share one's issue
-// slots and it no longer pays. The largest teams, whose steps are the longest,
-// come first: each takes the fewest envs per wavefront that keep the launch
-// within one wavefront per SIMD. Measured per step: 1024 envs of 8 in 128
-// wavefronts 2.20 us, in 1024 1.80 us; of 16 6.46 and 4.99 us; the mixed batch
-// of 8192 (2 to 12 robots) with its 12-robot envs four to a wavefront (898 in
-// all) 3.39 us, three (966) 3.05 us, one (1512) 3.70 us.
+// make its steps shorter. The largest teams, whose steps are the longest, come
+// first: each takes the fewest envs per wavefront that keep the launch within
+// one wavefront per SIMD, and in 16-lane groups within two, the most a SIMD
+// holds: their solves stall more than they issue. Measured per step: 1024 envs
+// of 8 in 128 wavefronts 2.20 us, in 1024 1.80 us; 3000 of 6 2.34 us in 750,
+// 2.42 us in 1500; 2000 of 16 6.25 us in 1000, 6.02 us in 2000; 4096 of 12
+// 4.56 us in 1024, 4.37 us in 2048 and 7.2 us in 4096; the mixed batch of 8192
+// (2 to 12 robots) with its 12-robot envs four to a wavefront (898 in all)
+// 3.91 us, three (966) 3.59 us, one (1512) 3.37 us.
 template <typename Count>
 __host__ __device__ inline void spread_envs(const Count *total, const int32_t *lanes, int simds,
                                             int32_t *epw) {
@@ -76,8 +78,9 @@ __host__ __device__ inline void spread_envs(const Count *total, const int32_t *l
   for (int n = RS_MAX_ROBOTS; n >= 2; --n) {
     if (!automatic[n] || total[n] == 0) continue;
     const int others = tiles - (int)((total[n] + epw[n] - 1) / epw[n]);
-    if (others >= simds) continue;
-    const int e = (int)((total[n] + (simds - others) - 1) / (simds - others));
+    const int room = (lanes[n] > 8 ? 2 * simds : simds) - others;
+    if (room <= 0) continue;
+    const int e = (int)((total[n] + room - 1) / room);
     if (e < epw[n]) {
       epw[n] = e;
       tiles = others + (int)((total[n] + e - 1) / e);
