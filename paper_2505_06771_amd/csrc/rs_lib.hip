@@ -79,14 +79,19 @@ template <int G> __device__ __forceinline__ int wave_env(int E, int epw, int lan
   own = grp < held;
   return e0 + (own ? grp : grp % held);
 }
-// Envs per wavefront: 64 / G, fewer while SIMDs are idle (a wavefront runs the
-// solver stages that any of its envs needs: one FP64 env of 4 robots, 1000
-// steps, 1.21 ms with the wavefront's other lanes off, 1.16 ms with them
-// running along; 4096 envs x 4, one step from a loop, 8.2 us in 256 wavefronts,
-// 8.0 us in 1024).
-static int envs_per_wave(int E, int G, int simds) {
+// Envs per wavefront: 64 / G, fewer while that leaves room on the chip (a
+// wavefront runs the solver stages that any of its envs needs: one FP64 env of
+// 4 robots, 1000 steps, 1.21 ms with the wavefront's other lanes off, 1.16 ms
+// with them running along). Up to one wavefront per SIMD; two for FP32 16-lane
+// groups, whose solves stall more than they issue (one step of 2048 envs of
+// 16, replayed: 33.1 us in 512 wavefronts, 32.4 in 1024, 30.5 in 2048; FP64
+// 40.9 in 1024, 44.2 in 2048). One step or certificate of up to four robots is
+// short beside starting its wavefronts: one per CU (4096 envs of 4, replayed:
+// 5.25 us in 256 wavefronts, 5.63 in 1024; env_steps 1.88 and 1.74 us a step).
+template <typename T> static int envs_per_wave(int E, int G, int num_cus, bool once) {
+  const int room = num_cus * (G > 8 && sizeof(T) == 4 ? 8 : G > 4 || !once ? 4 : 1);
   int n = 1;
-  while (n < 64 / G && (E + n - 1) / n > simds) n *= 2;
+  while (n < 64 / G && (E + n - 1) / n > room) n *= 2;
   return n;
 }
 static_assert(kQPStats == RS_QPS_COUNT, "qp_stats layout of robostep.h");
@@ -377,7 +382,7 @@ static rs_status do_env_step(rs_ctx *ctx, const rs_params *p, const rs_batch *b,
   A.qp_stats = qp_stats;
   A.qp_fail = ctx->qp_fail;
   const int G = pow2_group(A.N);
-  A.epw = envs_per_wave(A.E, G, 4 * ctx->num_cus);
+  A.epw = envs_per_wave<T>(A.E, G, ctx->num_cus, true);
   if (p->scenario == RS_SCN_PREDATOR_PREY) {
     RS_DISPATCH_G(G, hipLaunchKernelGGL((k_env_step<T, GG, true>), dim3((A.E + A.epw - 1) / A.epw),
                                         dim3(kBlock), 0, st, A));
@@ -405,7 +410,7 @@ static rs_status do_env_steps(rs_ctx *ctx, const rs_params *p, const rs_batch *b
   A.qp_stats = qp_stats;
   A.qp_fail = ctx->qp_fail;
   const int G = pow2_group(A.N);
-  A.epw = envs_per_wave(A.E, G, 4 * ctx->num_cus);
+  A.epw = envs_per_wave<T>(A.E, G, ctx->num_cus, false);
   if (p->scenario == RS_SCN_PREDATOR_PREY) {
     RS_DISPATCH_G(G, hipLaunchKernelGGL((k_env_steps<T, GG, true>), dim3((A.E + A.epw - 1) / A.epw),
                                         dim3(kBlock), 0, st, A));
@@ -455,7 +460,7 @@ static rs_status do_barrier(rs_ctx *ctx, const rs_params *p, int E, int N, const
   A.qp_stats = qp_stats;
   A.qp_fail = ctx->qp_fail;
   const int G = pow2_group(N);
-  A.epw = envs_per_wave(E, G, 4 * ctx->num_cus);
+  A.epw = envs_per_wave<T>(E, G, ctx->num_cus, true);
   RS_DISPATCH_G(G, hipLaunchKernelGGL((k_barrier<T, GG>), dim3((E + A.epw - 1) / A.epw), dim3(kBlock),
                                       0, st, A));
   return launch_status("barrier_certificate");

@@ -23,7 +23,7 @@ def _states(seed, E, n):
 
 
 @pytest.mark.parametrize("kind", ["f32", "f64"])
-@pytest.mark.parametrize("n,E", [(2, 9000), (3, 4097), (7, 2051), (16, 1030)])
+@pytest.mark.parametrize("n,E", [(2, 300), (2, 9000), (3, 4097), (7, 2051), (16, 1030), (16, 2051)])
 def test_large_batch_equals_small_ones(n, E, kind):
     import torch
 
