@@ -254,7 +254,7 @@ template <typename T> struct QPLoopOut {
 // the few wavefronts that need it. Refactoring the Gram system serially on
 // every step instead, from scratch, took 1.53 ms for one env_step of 16384
 // envs x 16 robots, a dense eighth of them, and 0.32 ms for 8192 x 12
-// certificates; this takes 0.21 and 0.06 ms.
+// certificates; this takes 0.19 and 0.06 ms.
 //
 // Explicit updates of H lose digits over many steps, so once no row is
 // violated the command and the multipliers are formed again from the active
@@ -262,7 +262,7 @@ template <typename T> struct QPLoopOut {
 // itself) and scanned again; a correction that does not close the residual
 // rebuilds H from the rows.
 //
-// Entry (qp_handover, written by the register loop): the problem and the
+// Entry (handover, written by the register loop): the problem and the
 // active bounds of every lane, and with `carry` the loop's q0 pair rows, the
 // entering row and its multiplier; (ux, uy) is the command of that active
 // set. Without `carry` it starts from the box clip. `iters` counts on from the
