@@ -99,6 +99,9 @@ __device__ __forceinline__ double tabs(double a) { return __builtin_fabs(a); }
 // division.
 __device__ __forceinline__ float qdiv(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 __device__ __forceinline__ double qdiv(double a, double b) { return a / b; }
+template <typename T> __device__ __forceinline__ T eps_v();  // spacing of the numbers at 1
+template <> __device__ __forceinline__ float eps_v<float>() { return 1.1920929e-7f; }
+template <> __device__ __forceinline__ double eps_v<double>() { return 2.220446049250313e-16; }
 template <typename T> __device__ __forceinline__ T big_v();
 template <> __device__ __forceinline__ float big_v<float>() { return 3.0e38f; }
 template <> __device__ __forceinline__ double big_v<double>() { return 1.0e300; }
@@ -464,23 +467,30 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
     return indep;
   };
   // command and multipliers from the active rows: one correction of the
-  // multipliers by H times the rows' residuals; returns the largest residual
-  // that was left after it
-  auto refine = [&]() {
+  // multipliers by H times the rows' residuals. Returns the largest residual
+  // over its row's norm that was left after it, and in `size` the largest sum
+  // of magnitudes that a coordinate of the command was formed from: a residual
+  // cannot fall below its rounding, in whatever unit the speeds are. (Formed
+  // here, in the sum that it belongs to: a loop of its own cost the solver's
+  // registers, and 16384 x 16 steps 50%.)
+  auto refine = [&](T &size) {
     T left = T(0);
     for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
       for (int s = 0; s < S; ++s)
         if (i + s * G < q) work(i + s * G) = lam[i + s * G];
       wave_lds_fence();
-      T vx = uhx, vy = uhy;
+      T vx = uhx, vy = uhy, ax = tabs(uhx), ay = tabs(uhy);
 #pragma unroll 4
       for (int a = 0; a < q; ++a) {
         const Row w = rows[a];
         const T f = T((i == ((int)w.x >> 8)) - (i == ((int)w.x & 255))) * w.w;
         vx -= f * w.y;
         vy -= f * w.z;
+        ax += tabs(f * w.y);
+        ay += tabs(f * w.z);
       }
+      size = on ? tmax(ax, ay) : T(0);
       ux = on ? vx : ux;
       uy = on ? vy : uy;
       const T bx = fx > 0 ? hix : lox, by = fy > 0 ? hiy : loy;
@@ -502,7 +512,8 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
         e[s] = bound ? w.y * (bax - uax) + w.z * (bay - uay)
                      : w.y * (ubx - uax) + w.z * (uby - uay) - beta;
         e[s] = k < q ? e[s] : T(0);
-        worst = tmax(worst, tabs(e[s]));
+        const T rn = bound ? T(1) : T(0.35355339059327373) * rsqrt_t(d2);  // 1 / |c|
+        worst = tmax(worst, k < q ? tabs(e[s]) * rn : T(0));
       }
       left = gmax<G>(worst);
       if (pass == 1) break;
@@ -520,6 +531,7 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
     }
     if (fx != 0) ux = fx > 0 ? hix : lox;
     if (fy != 0) uy = fy > 0 ? hiy : loy;
+    size = gmax<G>(size);
     return left;
   };
 
@@ -581,7 +593,10 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
       gargmax_payload<G>(best, bid, bcx, bcy, bb);
       if (bid < 0) {
         if (settled) break;  // optimal
-        settled = refine() <= (again ? T(8) * tol_add : tol_add);
+        T size;
+        const T left = refine(size);
+        const T close = tol_add + T(8) * eps_v<T>() * size;
+        settled = left <= (again ? T(8) * close : close);
         if (!settled && again) { out.status = 2; break; }
         stale = again = !settled;
         continue;
