@@ -34,7 +34,12 @@ HIPCC_FLAGS = [
 # bound by instruction latency: the backend's max-ILP scheduling strategy
 # interleaves its independent dependency chains better there (it shortened
 # launches by about 1% in same-box comparisons; on env_run it does not help).
+# rs_lib.hip: blocks that are only jumped to start on an instruction cache
+# line. A kernel that runs one wavefront per SIMD waits for each line it enters,
+# and where its blocks fall moves its time by 3% (one FP64 env of 4 robots, 1000
+# steps: 1.14 ms unaligned, 1.12 ms so, with other code around it 1.11 to 1.16).
 FILE_FLAGS = {
+    "rs_lib.hip": ["-mllvm", "-align-all-nofallthru-blocks=6"],
     "rs_rollout.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
     "rs_rollout_split.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
 }

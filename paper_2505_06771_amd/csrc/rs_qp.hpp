@@ -12,7 +12,8 @@
 //     with up to four active pairwise rows S the Gram system over the free
 //     coordinates, G_S = C_S^free C_S^free^T, is factored by Cholesky in
 //     registers; beyond that the inverse Gram matrix of all active rows, bounds
-//     among them, is kept in LDS;
+//     among them, is kept in LDS (and what that does not solve is solved again
+//     with the free coordinates' Gram system, factored in LDS);
 //   * the start point clips u_nom to the box, which is exactly the state after
 //     adding every violated bound (they are mutually orthogonal);
 //   * each iteration adds the most violated row (normalised violation),
@@ -29,6 +30,8 @@
 // done identically by every lane of the group from group-uniform data; the
 // general solver gives each lane two rows of the inverse.
 #pragma once
+
+#include <cstddef>
 
 #include "rs_device.hpp"
 
@@ -52,6 +55,7 @@ template <typename T, int G> struct alignas(4 * sizeof(T)) QPScratch {
   typename QPRow<T>::vec row[2 * G];  // active rows
   T lam[2 * G];                       // multipliers (objective 1/2 |u - u_nom|^2)
   T H[(2 * G) * (2 * G + 1) / 2];     // inverse Gram matrix of the rows (packed lower)
+  T px[G], py[G];                     // projection points, for the out-of-line solvers
 };
 // The scratch as an LDS pointer: an out-of-line function that took a generic
 // one would reach it by flat accesses, which also wait for the wavefront's
@@ -60,18 +64,6 @@ template <typename T, int G>
 using LdsScratch = __attribute__((address_space(3))) QPScratch<T, G>;
 
 __device__ __forceinline__ int tri(int a, int b) { return (a * (a + 1)) / 2 + b; }
-
-// Owner lane and rotation distance of pair (a, b), a < b, among N robots.
-__device__ __forceinline__ void pair_owner(int a, int b, int N, int &owner, int &k) {
-  const int d = b - a;
-  if (2 * d <= N) {
-    owner = a;
-    k = d;
-  } else {
-    owner = b;
-    k = N - d;
-  }
-}
 
 // Index of pair (a, b), a < b, in lexicographic order.
 __device__ __forceinline__ int pair_index(int a, int b, int N) {
@@ -243,7 +235,8 @@ template <int G> __device__ __forceinline__ void pair_owner_g(int a, int b, int 
 template <typename T> struct QPLoopOut {
   T ux, uy;
   int status, iters, q;
-  int in_lds;  // the general solver ran: 1 from the clip, 2 from the loop's active set
+  int in_lds;  // the general solver ran: 1 from the clip, 2 from the loop's active set,
+               // 3 without an answer
 };
 
 // General solver: the dual active-set method for any number of active rows,
@@ -272,25 +265,30 @@ template <typename T> struct QPLoopOut {
 // caller's. Every lane of the group calls it together; the rows stay in
 // sh->row / sh->lam.
 // What the register loop leaves in the group's scratch for the general solver:
-// twelve values per lane at the end of it (value c of lane i at c * G + i) and,
-// ahead of them, rows 0..3 {id, cx, cy, multiplier}, row 4 the entering row
-// {id, cx, cy, rhs} and its multiplier. With the problem in LDS the register
+// ten values per lane at the end of H (value c of lane i at c * G + i) beside
+// the projection points and, ahead of them, rows 0..3 {id, cx, cy,
+// multiplier}, row 4 the entering row {id, cx, cy, rhs} and its multiplier. With the problem in LDS the register
 // loop can end in a tail call of the general solver, which leaves it a leaf
 // function: as an ordinary caller it saved more registers on every entry (1%
 // of the headline rollout's time), and a second call site in the step loop
 // cost that loop 2 to 4%.
-constexpr int kHandover = 12;
-template <typename T, int G>
+// The general solver leaves the first six of them for qp_factored in the same
+// way, clear of all rows.
+constexpr int kHandover = 10, kHandback = 6;
+template <int VALUES, typename T, int G>
 __device__ __forceinline__ __attribute__((address_space(3))) T *handover(LdsScratch<T, G> *sh) {
-  static_assert(G == 2 || sizeof(QPScratch<T, G>) / sizeof(T) >= 24 + kHandover * G, "rows fit");
-  static_assert(sizeof(QPScratch<T, G>) / sizeof(T) >= kHandover * G, "lanes fit");
-  return (__attribute__((address_space(3))) T *)(sh + 1) - kHandover * G;
+  typedef QPScratch<T, G> Scratch;
+  constexpr int end = offsetof(Scratch, px) / sizeof(T);
+  static_assert(end >= VALUES * G && (G == 2 || end >= 24 + VALUES * G), "row 5 stays clear");
+  static_assert(VALUES > kHandback || end >= (2 * G) * 4 + VALUES * G, "all rows stay clear");
+  return (__attribute__((address_space(3))) T *)sh->px - VALUES * G;
 }
 
 template <typename T, int G>
 __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane, int N, bool carry,
                                                  QPLoopOut<T> &out, T rs2, T gamma, T vmax4,
-                                                 T tol_add, T eps_z, T eps_r, int qp_cap) {
+                                                 T tol_add, T eps_z, T eps_r, int qp_cap,
+                                                 typename QPRow<T>::vec &enter) {
   constexpr int KH = G / 2;
   constexpr int S = 2;  // slots per lane: i and i + G
   const T BIG = big_v<T>();
@@ -305,11 +303,11 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
   const int gbase = lane & ~(G - 1);
   const int cap = qp_cap > 0 ? qp_cap : 8 * N + 32;
   // --- what the register loop left ---------------------------------------------
-  const LdsT *hv = handover<T, G>(sh) + i;
-  const T px = hv[0], py = hv[G], uhx = hv[2 * G], uhy = hv[3 * G];
-  const T lox = hv[4 * G], hix = hv[5 * G], loy = hv[6 * G], hiy = hv[7 * G];
-  int fx = (int)hv[8 * G], fy = (int)hv[9 * G];
-  T mux = hv[10 * G], muy = hv[11 * G];
+  const LdsT *hv = handover<kHandover>(sh) + i;
+  const T px = sh->px[i], py = sh->py[i], uhx = hv[0], uhy = hv[G];
+  const T lox = hv[2 * G], hix = hv[3 * G], loy = hv[4 * G], hiy = hv[5 * G];
+  int fx = (int)hv[6 * G], fy = (int)hv[7 * G];
+  T mux = hv[8 * G], muy = hv[9 * G];
   Row p = (Row){T(0), T(0), T(0), T(0)};  // the entering row
   T lam_p = T(0), hl = T(0);              // its multiplier; lane k < 4: row k's
   if constexpr (G > 2) {
@@ -370,15 +368,11 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
     const int qx = q0 + __popc(bx);
     const int sx = q0 + __popc(bx & below), sy = qx + __popc(by & below);
     q = qx + __popc(by);
-    if (q > 2 * G) {
-      out = QPLoopOut<T>{ux, uy, 2, out.iters + iters0, 0, out.in_lds};
-      return;
-    }
-    if (fx != 0) {
+    if (fx != 0 && q <= 2 * G) {
       rows[sx] = (Row){T(i | kNoRobot << 8), T(-fx), T(0), T(0)};
       lam[sx] = mux;
     }
-    if (fy != 0) {
+    if (fy != 0 && q <= 2 * G) {
       rows[sy] = (Row){T(i | kNoRobot << 8), T(0), T(-fy), T(0)};
       lam[sy] = muy;
     }
@@ -548,7 +542,7 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
   T cx = p.y, cy = p.z, rhs = p.w;
   while (true) {
     if (stale) {
-      if (!rebuild(q)) { out.status = 2; q = 0; break; }
+      if (q > 2 * G || !rebuild(q)) { out.status = 2; break; }
       stale = false;
     }
     if (!pend) {
@@ -724,16 +718,293 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
 
   if (dead) {
     out.status = 1;
-    q = 0;
     if (on) {
       ux = lox <= hix ? tmin(tmax(uhx, lox), hix) : T(0.5) * (lox + hix);
       uy = loy <= hiy ? tmin(tmax(uhy, loy), hiy) : T(0.5) * (loy + hiy);
     }
   }
+  if (out.status != 0) {  // for qp_factored to confirm
+    LdsT *hw = handover<kHandback>(sh) + i;
+    wave_lds_fence();
+    const T v[kHandback] = {uhx, uhy, lox, hix, loy, hiy};
+#pragma unroll
+    for (int c = 0; c < kHandback; ++c) hw[c * G] = v[c];
+    wave_lds_fence();
+    out.in_lds = 3;
+    enter = (Row){T(ra | rb << 8), cx, cy, T(0)};
+  }
   out.ux = ux;
   out.uy = uy;
   out.q = q;
   out.iters += iters0;
+}
+
+// The dual active-set method once more, from the box clip, with the Gram system
+// of the active pair rows over the coordinates that no active bound fixes,
+// factored anew on every step (serially, every lane of the group alike): for
+// what the general solver did not solve. Its inverse holds the bounds as rows
+// of their own, so a pair row of which the bounds leave only a sliver (two
+// robots held along their line of centres, met by the small component across
+// it) is too close to dependent on them; without the bounds it is an ordinary
+// row. An overlapping pair held at the walls, met by 4e-6 m/s across: called
+// infeasible in FP32 below 3e-5 rad off the axis without this.
+// A verdict of "infeasible" stands unless such a row (under 0.1% of its squared
+// norm free) is among the active ones or entering; "not solved" never does. Signature and `packed` as qp_general;
+// groups whose in_lds is not 3 pass through. fpb, fdx, fdy: the row that could
+// not enter.
+template <typename T, int G>
+__device__ __noinline__ QPLoopOut<T> qp_factored(LdsScratch<T, G> *sh, int lane, int packed, int N,
+                                                 bool on, T px, T py, T ux, T uy, T lox, T hix,
+                                                 T loy, T hiy, bool seed, int iters, int fpb, T fl1,
+                                                 T fdx, T fdy, T rs2, T gamma, T vmax4, T tol_add,
+                                                 T eps_z, T eps_r, int qp_cap, bool want_rows) {
+  typedef typename QPRow<T>::vec Row;
+  typedef __attribute__((address_space(3))) Row LdsRow;
+  typedef __attribute__((address_space(3))) T LdsT;
+  const T BIG = big_v<T>();
+  LdsRow *rows = sh->row;
+  LdsT *lam = sh->lam, *L = sh->H;
+  auto work = [&](int k) -> LdsT & { return ((LdsT *)(rows + k))[3]; };
+  const int i = lane & (G - 1), base = lane & ~(G - 1);
+  const int cap = qp_cap > 0 ? qp_cap : 8 * N + 32;
+  on = i < N;
+  QPLoopOut<T> out{ux, uy, (packed >> 8) & 255, iters, packed >> 16, packed & 255};
+  bool solve = out.in_lds == 3;
+  // the part of robot r's (xx, yy) along the coordinates whose bits are set
+  auto over = [](uint32_t x, uint32_t y, int r, T xx, T yy) {
+    return ((x >> r) & 1u ? xx : T(0)) + ((y >> r) & 1u ? yy : T(0));
+  };
+  if (solve && out.status == 1) {
+    uint32_t freex = ~0u, freey = ~0u;
+    auto row = [&](int k) { return k < out.q ? rows[k] : (Row){T(fpb), fdx, fdy, T(0)}; };
+    for (int k = 0; k <= out.q; ++k) {
+      const Row w = row(k);
+      if ((int)w.x >> 8 == kNoRobot) {
+        const uint32_t bit = ~(1u << ((int)w.x & 255));
+        if (w.y != T(0)) freex &= bit;
+        else freey &= bit;
+      }
+    }
+    solve = false;
+    for (int k = 0; k <= out.q; ++k) {
+      const Row w = row(k);
+      if ((int)w.x >> 8 == kNoRobot) continue;
+      const T xx = w.y * w.y, yy = w.z * w.z;
+      const T left = over(freex, freey, (int)w.x & 255, xx, yy) +
+                     over(freex, freey, (int)w.x >> 8, xx, yy);
+      solve = solve || (left > T(0) && left < T(0.002) * (xx + yy));  // |c|^2 = 2 (xx + yy)
+    }
+    out.q = 0;
+  }
+  if (solve) {
+    const LdsT *hv = handover<kHandback>(sh) + i;
+    px = sh->px[i];
+    py = sh->py[i];
+    const T uhx = hv[0], uhy = hv[G];
+    lox = hv[2 * G]; hix = hv[3 * G]; loy = hv[4 * G]; hiy = hv[5 * G];
+    wave_lds_fence();
+    int fx = 0, fy = 0;  // +1 fixed at upper, -1 fixed at lower
+    T mux = T(0), muy = T(0);
+    ux = uhx;
+    uy = uhy;
+    if (on) {
+      if (uhx > hix) { ux = hix; fx = 1; mux = uhx - hix; }
+      else if (uhx < lox) { ux = lox; fx = -1; mux = lox - uhx; }
+      if (uhy > hiy) { uy = hiy; fy = 1; muy = uhy - hiy; }
+      else if (uhy < loy) { uy = loy; fy = -1; muy = loy - uhy; }
+    }
+    int q = 0, steps = 0, status = 0;
+    uint32_t own_act = 0;  // bit K: my rotation-K pair is active
+    bool dead = false;
+    while (!dead && status == 0) {
+      // --- most violated row (normalised) --------------------------------------
+      T best = tol_add;
+      int bid = -1;  // pair: a << 4 | b; bound: 256 + 4 robot + 2 coordinate + lower
+      if (on) {
+        if (fx == 0) {
+          const T su = ux - hix, sl = lox - ux;
+          if (su > best) { best = su; bid = 256 + 4 * i; }
+          else if (sl > best) { best = sl; bid = 256 + 4 * i + 1; }
+        }
+        if (fy == 0) {
+          const T su = uy - hiy, sl = loy - uy;
+          if (su > best) { best = su; bid = 256 + 4 * i + 2; }
+          else if (sl > best) { best = sl; bid = 256 + 4 * i + 3; }
+        }
+      }
+      for (int K = 1; K <= G / 2; ++K) {
+        const int j = (i + K) & (G - 1);
+        const T pxj = __shfl(px, base + j, 64), pyj = __shfl(py, base + j, 64);
+        const T uxj = __shfl(ux, base + j, 64), uyj = __shfl(uy, base + j, 64);
+        if (on && j < N && !(2 * K == G && i >= K) && !((own_act >> K) & 1u)) {
+          const bool ia = i < j;
+          const T dx = ia ? px - pxj : pxj - px, dy = ia ? py - pyj : pyj - py;
+          const T d2 = dx * dx + dy * dy;
+          const T h = d2 - rs2;
+          const T bb = gamma * (h * h * h);
+          if (d2 > T(0) && vmax4 * (tabs(dx) + tabs(dy)) > bb) {
+            const T dux = ia ? uxj - ux : ux - uxj, duy = ia ? uyj - uy : uy - uyj;
+            const T sn = (T(2) * (dx * dux + dy * duy) - bb) * (T(0.35355339059327373) * rsqrt_t(d2));
+            if (sn > best) { best = sn; bid = min(i, j) << 4 | max(i, j); }
+          }
+        }
+      }
+      gargmax<G>(best, bid);
+      if (bid < 0) break;  // optimal
+      if (++steps > cap) { status = 2; break; }
+      // the entering row: coefficients (-cx, -cy) at robot pa, (cx, cy) at pb; a
+      // bound: minus its unit normal, pb = kNoRobot
+      const bool pair = bid < 256;
+      const int pa = pair ? bid >> 4 : (bid - 256) >> 2, pb = pair ? bid & 15 : kNoRobot;
+      T cx, cy, rhs;
+      {
+        const int jb = base + (pair ? pb : pa);
+        const T dx = __shfl(px, base + pa, 64) - __shfl(px, jb, 64);
+        const T dy = __shfl(py, base + pa, 64) - __shfl(py, jb, 64);
+        const T h = dx * dx + dy * dy - rs2;
+        const T lim = (bid & 2) ? ((bid & 1) ? -loy : hiy) : ((bid & 1) ? -lox : hix);
+        const T blim = __shfl(lim, base + pa, 64);
+        const T sg = (bid & 1) ? T(1) : T(-1);
+        cx = pair ? T(2) * dx : ((bid & 2) ? T(0) : sg);
+        cy = pair ? T(2) * dy : ((bid & 2) ? sg : T(0));
+        rhs = pair ? gamma * (h * h * h) : blim;
+      }
+      T lam_p = T(0);
+      bool added = false;
+      while (!added) {
+        const uint32_t freex = ~group_bits<G>(__ballot(fx != 0), lane);
+        const uint32_t freey = ~group_bits<G>(__ballot(fy != 0), lane);
+        // product of two rows over the free coordinates
+        auto gram = [&](Row s, int ta, int tb, T tx, T ty) {
+          const int sa = (int)s.x & 255, sb = (int)s.x >> 8;
+          const T xx = s.y * tx, yy = s.z * ty;
+          T acc = T(0);
+          if (sa == ta) acc += over(freex, freey, sa, xx, yy);
+          if (sa == tb) acc -= over(freex, freey, sa, xx, yy);
+          if (sb == ta) acc -= over(freex, freey, sb, xx, yy);
+          if (sb == tb) acc += over(freex, freey, sb, xx, yy);
+          return acc;
+        };
+        // Cholesky factor of the active rows, then r = G^-1 (C c) in the work column
+        bool chol_ok = true;
+        for (int a = 0; a < q && chol_ok; ++a) {
+          const Row w = rows[a];
+          for (int b = 0; b <= a; ++b) {
+            T v = gram(rows[b], (int)w.x & 255, (int)w.x >> 8, w.y, w.z);
+            for (int k = 0; k < b; ++k) v -= L[tri(a, k)] * L[tri(b, k)];
+            if (a == b) {
+              chol_ok = v > T(0);
+              if (chol_ok) L[tri(a, a)] = sqrt_t(v);
+            } else {
+              L[tri(a, b)] = v / L[tri(b, b)];
+            }
+          }
+        }
+        if (!chol_ok) { status = 2; break; }
+        for (int a = 0; a < q; ++a) {
+          T g = gram(rows[a], pa, pb, cx, cy);
+          for (int k = 0; k < a; ++k) g -= L[tri(a, k)] * work(k);
+          work(a) = g / L[tri(a, a)];
+        }
+        for (int a = q - 1; a >= 0; --a) {
+          T v = work(a);
+          for (int k = a + 1; k < q; ++k) v -= L[tri(k, a)] * work(k);
+          work(a) = v / L[tri(a, a)];
+        }
+        // the row less its part in the active ones, at my robot: along free
+        // coordinates the step, along fixed ones the change of my bounds
+        const int sg = (i == pb) - (i == pa);
+        T zx = T(sg) * cx, zy = T(sg) * cy;
+        for (int a = 0; a < q; ++a) {
+          const Row w = rows[a];
+          const T f = T((i == ((int)w.x >> 8)) - (i == ((int)w.x & 255))) * w.w;
+          zx -= f * w.y;
+          zy -= f * w.z;
+        }
+        if (!on) zx = zy = T(0);
+        const T rfx = T(fx) * zx, rfy = T(fy) * zy;
+        zx = fx == 0 ? zx : T(0);
+        zy = fy == 0 ? zy : T(0);
+        const T zz = gsum<G>(zx * zx + zy * zy);
+        const T xx = cx * cx, yy = cy * cy;
+        const T n2 = over(freex, freey, pa, xx, yy) + (pair ? over(freex, freey, pb, xx, yy) : T(0));
+        const T sp = gsum<G>(on ? T(sg) * (cx * ux + cy * uy) : T(0)) - rhs;
+        // blocking row: the first active multiplier to reach zero
+        T t1 = BIG;
+        int drop = -1;  // pair slot, or 1024 + 2 robot + coordinate
+        for (int a = 0; a < q; ++a) {
+          const T ra = work(a), ratio = qdiv(lam[a], ra);
+          if (ra > eps_r && ratio < t1) { t1 = ratio; drop = a; }
+        }
+        if (rfx > eps_r) {
+          const T ratio = qdiv(mux, rfx);
+          if (ratio < t1) { t1 = ratio; drop = 1024 + 2 * i; }
+        }
+        if (rfy > eps_r) {
+          const T ratio = qdiv(muy, rfy);
+          if (ratio < t1) { t1 = ratio; drop = 1024 + 2 * i + 1; }
+        }
+        gargmin<G>(t1, drop);
+        const bool z_ok = zz > eps_z * n2;
+        const T t2 = z_ok ? qdiv(sp, zz) : BIG;
+        if (drop < 0 && !z_ok) { dead = true; break; }  // no step can restore the row
+        const bool full = z_ok && (drop < 0 || t2 <= t1);
+        const T t = full ? t2 : t1;
+        if (full && pair && q == 2 * G) { status = 2; break; }
+        if (z_ok) {
+          ux -= t * zx;
+          uy -= t * zy;
+        }
+        for (int a = 0; a < q; ++a) lam[a] = lam[a] - t * work(a);
+        mux -= t * rfx;
+        muy -= t * rfy;
+        lam_p += t;
+        if (full) {
+          if (pair) {
+            rows[q] = (Row){T(pa | pb << 8), cx, cy, T(0)};
+            lam[q] = lam_p;
+            ++q;
+            int owner, kk;
+            pair_owner_g<G>(pa, pb, owner, kk);
+            if (i == owner) own_act |= 1u << kk;
+          } else if (i == pa) {
+            // (cx, cy) is minus the normal: negative at an upper bound
+            if (cx != T(0)) { fx = cx < T(0) ? 1 : -1; mux = lam_p; ux = cx < T(0) ? hix : lox; }
+            else { fy = cy < T(0) ? 1 : -1; muy = lam_p; uy = cy < T(0) ? hiy : loy; }
+          }
+          added = true;
+        } else if (drop >= 1024) {
+          if (i == (drop - 1024) >> 1) {
+            if (drop & 1) { fy = 0; muy = T(0); }
+            else { fx = 0; mux = T(0); }
+          }
+        } else {
+          const int id = (int)rows[drop].x;
+          int owner, kk;
+          pair_owner_g<G>(id & 255, id >> 8, owner, kk);
+          if (i == owner) own_act &= ~(1u << kk);
+          for (int a = drop; a + 1 < q; ++a) {
+            rows[a] = rows[a + 1];
+            lam[a] = lam[a + 1];
+          }
+          --q;
+        }
+        if (++steps > cap) { status = 2; break; }
+      }
+    }
+    if (dead) {
+      status = 1;
+      q = 0;
+      if (on) {
+        ux = tmin(tmax(uhx, lox), hix);
+        uy = tmin(tmax(uhy, loy), hiy);
+      }
+    }
+    wave_lds_fence();
+    out = QPLoopOut<T>{ux, uy, status, out.iters + steps, q, 3};
+  }
+  __builtin_amdgcn_s_setprio(0);
+  return out;
 }
 
 // Tail of the register loop for a wavefront in which some group needs the
@@ -748,9 +1019,15 @@ __device__ __noinline__ QPLoopOut<T> qp_general(LdsScratch<T, G> *sh, int lane, 
                                                 T fdx, T fdy, T rs2, T gamma, T vmax4, T tol_add,
                                                 T eps_z, T eps_r, int qp_cap, bool want_rows) {
   QPLoopOut<T> out{ux, uy, (packed >> 8) & 255, iters, packed >> 16, packed & 255};
+  typename QPRow<T>::vec p{};
   if (out.in_lds != 0)
     qp_general_solve<T, G>(sh, lane, N, out.in_lds == 2, out, rs2, gamma, vmax4, tol_add, eps_z,
-                           eps_r, qp_cap);
+                           eps_r, qp_cap, p);
+  if (__ballot(out.in_lds == 3) != 0)  // wavefront-uniform: a tail call
+    [[clang::musttail]] return qp_factored<T, G>(
+        sh, lane, out.in_lds | out.status << 8 | out.q << 16, N, true, T(0), T(0), out.ux, out.uy,
+        T(0), T(0), T(0), T(0), false, out.iters, (int)p.x, T(0), p.y, p.z, rs2, gamma, vmax4,
+        tol_add, eps_z, eps_r, qp_cap, false);
   __builtin_amdgcn_s_setprio(0);
   return out;
 }
@@ -807,10 +1084,9 @@ __device__ __noinline__ QPLoopOut<T> qp_active_set(LdsScratch<T, G> *sh, int lan
     crn[K - 1] = d2 > T(0) ? T(0.35355339059327373) * rsqrt_t(d2) : T(0);
     cpid[K - 1] = (cand && d2 > T(0)) ? ((ia ? i : j) << 4 | (ia ? j : i)) : -1;
   });
-  // the projection points are not needed again here: into the hand-over's
-  // place now (clear of the row handed in through H), out of the registers
-  handover<T, G>(sh)[i] = px;
-  handover<T, G>(sh)[G + i] = py;
+  // the projection points are not needed again here: out of the registers
+  sh->px[i] = px;
+  sh->py[i] = py;
   // --- start: clip to the box; active bounds fix their coordinate ----------
   int fx = 0, fy = 0;
   T mux = T(0), muy = T(0);
@@ -1175,10 +1451,10 @@ __device__ __noinline__ QPLoopOut<T> qp_active_set(LdsScratch<T, G> *sh, int lan
     // from this active set; a degenerate Gram system: it starts from the clip
     typedef __attribute__((address_space(3))) T LdsT;
     out.in_lds = carry ? 2 : 1;
-    LdsT *hv = handover<T, G>(sh) + i;
-    const T v[kHandover - 2] = {uhx, uhy, lox, hix, loy, hiy, T(fx), T(fy), mux, muy};
+    LdsT *hv = handover<kHandover>(sh) + i;
+    const T v[kHandover] = {uhx, uhy, lox, hix, loy, hiy, T(fx), T(fy), mux, muy};
 #pragma unroll
-    for (int c = 2; c < kHandover; ++c) hv[c * G] = v[c - 2];
+    for (int c = 0; c < kHandover; ++c) hv[c * G] = v[c];
     if constexpr (G > 2) {
       if (carry) {
 #pragma unroll
