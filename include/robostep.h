@@ -355,7 +355,9 @@ typedef struct {
                                 0 = 64/lanes, fewer while SIMDs are idle (a wavefront
                                 runs the solver stages any of its envs needs, so fewer
                                 envs per wavefront run fewer of them per env, on more
-                                wavefronts) */
+                                wavefronts). [0]: bit N set = as if envs_per_wave[N]
+                                were 0; the autotuner sets it where [N] only reports
+                                what 0 gave on its batch (clear it to keep that) */
 } rs_schedule;
 
 rs_status rs_plan_create(rs_ctx *ctx, int32_t num_envs, const int32_t *robots_per_env,
@@ -444,7 +446,10 @@ rs_status env_run_noalloc(rs_ctx *ctx, const rs_params *p, const int32_t *robots
  * default on this workload. The tuning runs use the tuner's own failure
  * counters, not the context's. The schedule is
  * stored in the context (used by plans created afterwards with schedule NULL)
- * and returned in `out` (may be NULL). Allocates device scratch for the
+ * and returned in `out` (may be NULL), for every size tuned with the effective
+ * lanes, envs per wavefront and iteration cap; envs per wavefront that no
+ * candidate improved on are marked as automatic and follow the size of the
+ * batch wherever the schedule is used. Allocates device scratch for the
  * workload; RS_ERR_OUT_OF_MEMORY if that fails.
  * ------------------------------------------------------------------------- */
 rs_status rs_autotune(rs_ctx *ctx, const rs_params *p, const int32_t *robots, int32_t count,

@@ -583,7 +583,7 @@ static rs_status autotune_impl(rs_ctx *ctx, const rs_params *p, const std::vecto
           consider(c);
         }
         const int full = 64 / lanes_for(best, n);
-        for (int div = 2; div <= 8; div *= 2) {
+        for (int div = 1; div <= 8; div *= 2) {
           if (full / div < 1) break;
           rs_schedule c = best;
           c.envs_per_wave[n] = full / div;
@@ -596,7 +596,9 @@ static rs_status autotune_impl(rs_ctx *ctx, const rs_params *p, const std::vecto
           consider(c);
         }
       }
-      // report the effective values for the tuned sizes
+      // report the effective values for the tuned sizes; an automatic number of
+      // envs per wavefront stays automatic (it follows the batch: the one of a
+      // few hundred envs would run 16384 x 3 in 12.2 us a step, 2.1 with its own)
       int32_t total[RS_MAX_ROBOTS + 1] = {}, lanes[RS_MAX_ROBOTS + 1] = {}, epw[RS_MAX_ROBOTS + 1] = {};
       for (int32_t n : counts) ++total[n];
       for (int n = 2; n <= RS_MAX_ROBOTS; ++n) {
@@ -606,6 +608,7 @@ static rs_status autotune_impl(rs_ctx *ctx, const rs_params *p, const std::vecto
       spread_envs(total, lanes, 4 * ctx->num_cus, epw);
       for (int32_t n : sizes) {
         best.lanes_per_env[n] = lanes[n];
+        if (scheduled_envs_per_wave(best, n) == 0) best.envs_per_wave[0] |= 1 << n;
         best.envs_per_wave[n] = epw[n];
         if (best.qp_iters[n] <= 0) best.qp_iters[n] = 8 * n + 32;
       }

@@ -88,8 +88,10 @@ __host__ __device__ inline void spread_envs(const Count *total, const int32_t *l
   }
 }
 // The schedule's envs per wavefront for robot count n, 0 where it leaves them
-// to spread_envs.
+// to spread_envs (bit n of envs_per_wave[0]: the value there is what
+// spread_envs gave for the batch that the autotuner ran).
 inline int scheduled_envs_per_wave(const rs_schedule &sched, int n) {
+  if (((uint32_t)sched.envs_per_wave[0] >> n) & 1u) return 0;
   const int c = sched.envs_per_wave[n];
   return (c >= 1 && c <= 64 / lanes_for(sched, n)) ? c : 0;
 }
