@@ -141,7 +141,7 @@ __device__ void reset_env(ConstRef<T> K, uint32_t env_id, uint32_t episode, int 
 // robots for candidates i, i + G, ..., and one arg-max butterfly picks the
 // winner; with G = 2 a group minimum per candidate is as cheap.
 template <typename T, int G, typename CS>
-__device__ __forceinline__ void prey_move(const CS &C, QPScratch<T, G> *sh, int i,
+__device__ __forceinline__ void prey_move(const CS &C, QPScratch<T, G> *sh, int i, int N,
                                           bool on, T x, T y, T &qx, T &qy) {
   constexpr int NCAND = 17;
   constexpr double kC = 0.92387953251128674, kH = 0.70710678118654752, kS = 0.38268343236508977;
@@ -164,12 +164,16 @@ __device__ __forceinline__ void prey_move(const CS &C, QPScratch<T, G> *sh, int 
   };
   // squared distance to candidate k, the order of its rounding written out:
   // the arg-max decides between scores that may be equal but for it, so every
-  // kernel has to round them alike
+  // kernel has to round them alike, whatever the group's width (by the robot
+  // count, pairs one way and larger teams the other)
+  const bool two = G == 2 || N == 2;
   auto score = [&](auto kc, T ex, T ey) {
     constexpr int k = decltype(kc)::value;
     constexpr int q = k == 0 ? 0 : k - 1;
-    constexpr bool xfirst = k == 0 || (G == 2 ? dir_c[q] != 0 : dir_s[q] == 0);
-    return xfirst ? tfma(ex, ex, ey * ey) : tfma(ey, ey, ex * ex);
+    constexpr bool along_x = k == 0 || dir_s[q] == 0, along_y = k != 0 && dir_c[q] == 0;
+    const bool xfirst = along_x || (!along_y && two);
+    const T a = xfirst ? ex : ey, b = xfirst ? ey : ex;
+    return tfma(a, a, b * b);
   };
   if constexpr (G == 2 || sizeof(QPScratch<T, G>) < sizeof(T) * NCAND * G) {
     T best = T(-1), bx = qx, by = qy;
@@ -364,7 +368,7 @@ __device__ __forceinline__ StepOut<T> env_step_group(const KT &K, int qp_cap, QP
     const int base = lane & ~(G - 1);
     qx = __shfl(gx, base, 64);
     qy = __shfl(gy, base, 64);
-    prey_move<T, G>(*K.get(), sh, i, on, x, y, qx, qy);
+    prey_move<T, G>(*K.get(), sh, i, N, on, x, y, qx, qy);
   }
   T lox, hix, loy, hiy;
   wall_bounds(*K.get(), px, py, lox, hix, loy, hiy);
