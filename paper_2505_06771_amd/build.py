@@ -34,13 +34,15 @@ HIPCC_FLAGS = [
 # bound by instruction latency: the backend's max-ILP scheduling strategy
 # interleaves its independent dependency chains better there (it shortened
 # launches by about 1% in same-box comparisons; on env_run it does not help).
-# rs_lib.hip: blocks that are only jumped to start on an instruction cache
-# line. A kernel that runs one wavefront per SIMD waits for each line it enters,
-# and where its blocks fall moves its time by 3% (one FP64 env of 4 robots, 1000
-# steps: 1.14 ms unaligned, 1.12 ms so, with other code around it 1.11 to 1.16).
+# Blocks that are only jumped to start on an instruction cache line: a kernel of
+# one wavefront per SIMD waits for each line it enters, and where its blocks fall
+# moves its time by 3% (one FP64 env of 4 robots, 1000 steps: 1.14 ms unaligned,
+# 1.12 ms so, with other code around it 1.11 to 1.16; 43690 x 3 rollout 704.6 and
+# 701.7 us, 16384 x 8 595.7 and 594.5).
+ALIGN_BLOCKS = ["-mllvm", "-align-all-nofallthru-blocks=6"]
 FILE_FLAGS = {
-    "rs_lib.hip": ["-mllvm", "-align-all-nofallthru-blocks=6"],
-    "rs_rollout.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+    "rs_lib.hip": ALIGN_BLOCKS,
+    "rs_rollout.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp", *ALIGN_BLOCKS],
     "rs_rollout_split.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
 }
 # the host pass does not know the packed-fp32 feature; that warning is noise
