@@ -72,11 +72,6 @@ template <typename T> __device__ __forceinline__ T unit24_t(uint32_t r) {
 }
 
 // ---- lane-group primitives (groups are aligned blocks of G lanes) ----------
-template <int G, typename T> __device__ __forceinline__ T group_sum(T v) {
-#pragma unroll
-  for (int o = G / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 template <int G, typename T> __device__ __forceinline__ T group_max(T v) {
 #pragma unroll
   for (int o = G / 2; o > 0; o >>= 1) {
@@ -84,38 +79,6 @@ template <int G, typename T> __device__ __forceinline__ T group_max(T v) {
     v = w > v ? w : v;
   }
   return v;
-}
-template <int G, typename T> __device__ __forceinline__ T group_min(T v) {
-#pragma unroll
-  for (int o = G / 2; o > 0; o >>= 1) {
-    T w = __shfl_xor(v, o, 64);
-    v = w < v ? w : v;
-  }
-  return v;
-}
-// Arg-max with deterministic tie break on the smaller id; every lane of the
-// group ends with the same (value, id).
-template <int G, typename T> __device__ __forceinline__ void group_argmax(T &v, int &id) {
-#pragma unroll
-  for (int o = G / 2; o > 0; o >>= 1) {
-    T w = __shfl_xor(v, o, 64);
-    int j = __shfl_xor(id, o, 64);
-    if (w > v || (w == v && j < id)) {
-      v = w;
-      id = j;
-    }
-  }
-}
-template <int G, typename T> __device__ __forceinline__ void group_argmin(T &v, int &id) {
-#pragma unroll
-  for (int o = G / 2; o > 0; o >>= 1) {
-    T w = __shfl_xor(v, o, 64);
-    int j = __shfl_xor(id, o, 64);
-    if (w < v || (w == v && j < id)) {
-      v = w;
-      id = j;
-    }
-  }
 }
 // Bits of the group's lanes in a wave ballot, shifted down to bit 0.
 template <int G> __device__ __forceinline__ uint32_t group_bits(uint64_t ballot, int lane) {
