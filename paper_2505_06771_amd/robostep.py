@@ -184,8 +184,12 @@ def _stream(stream) -> Optional[int]:
         import torch
 
         # the handle of torch.cuda.current_stream() without the Stream object
-        # around it: 0.3 us of a call's 6 instead of 2.9 of 9
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        # around it: 0.3 us of a call's 6 instead of 2.9 of 9 (a function that
+        # torch does not document: without it, the public way)
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        except AttributeError:
+            return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
