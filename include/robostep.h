@@ -136,7 +136,7 @@ typedef struct rs_plan rs_plan;
  * from their Gram system (FP32 also takes this stage when a one-row guess
  * is rejected: the guessed row plus the row it violates; and for exactly
  * three violated rows); ACTIVE_SET: the
- * register-resident dual active-set loop; GENERAL: the general active-set
+ * register-resident dual active-set loop; GENERAL: a general active-set
  * solver with its rows in LDS), or INFEASIBLE (no feasible command) or
  * CAPPED (stopped by the iteration cap or a numerical failure). ITERATIONS
  * sums the active-set iterations of the solves that ran the loop. */
@@ -302,7 +302,8 @@ rs_status barrier_certificate(rs_ctx *ctx, const rs_params *p, int32_t num_envs,
  * state is left at the post-rollout state. Requires 2N+4 <= 32.
  * qp_stats [E][RS_QPS_COUNT] int32 (NULL ok) accumulates the certificate
  * statistics of all H steps; it selects a separately compiled kernel that
- * counts them (the kernel without it carries none of that code).
+ * counts them (the kernel without it carries none of that code) and packs
+ * every wavefront, so that small batches take up to twice as long with it.
  * The launch is captured once per (shape, pointers) in a hipGraph and replayed.
  * ------------------------------------------------------------------------- */
 rs_status rollout(rs_ctx *ctx, const rs_params *p, const rs_batch *b, const rs_policy *policy,

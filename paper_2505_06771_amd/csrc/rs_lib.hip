@@ -86,8 +86,13 @@ template <int G> __device__ __forceinline__ int wave_env(int E, int epw, int lan
 // groups, whose solves stall more than they issue (one step of 2048 envs of
 // 16, replayed: 33.1 us in 512 wavefronts, 32.4 in 1024, 30.5 in 2048; FP64
 // 40.9 in 1024, 44.2 in 2048). One step or certificate of up to four robots is
-// short beside starting its wavefronts: one per CU (4096 envs of 4, replayed:
-// 5.25 us in 256 wavefronts, 5.63 in 1024; env_steps 1.88 and 1.74 us a step).
+// short beside starting its wavefronts: one per CU. The line is a flat one: one
+// step with one, two and four wavefronts per CU, replayed, an eighth of the envs
+// clustered: 700 x 2 4.40, 4.34 and 4.22 us, 4000 x 2 4.51, 4.80 and 4.65, 300 x 4
+// 12.1, 11.2 and 11.2, 4000 x 4 24.7, 25.5 and 23.8, FP64 4000 x 3 14.8, 15.3 and
+// 16.1; after a reset 4000 x 4 4.72, 5.00 and 5.13; certificates of 4000 x 2 3.03,
+// 3.18 and 3.22, of 700 x 4 10.5, 10.3 and 9.9 (env_steps of 4096 x 4 1.88 us a
+// step with one and 1.74 with four).
 template <typename T> static int envs_per_wave(int E, int G, int num_cus, bool once) {
   const int room = num_cus * (G > 8 && sizeof(T) == 4 ? 8 : G > 4 || !once ? 4 : 1);
   int n = 1;

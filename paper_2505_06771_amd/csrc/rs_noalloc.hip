@@ -153,7 +153,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_noalloc_plan(PlanArgs P) {
         ib += c;
       }
       spread_envs(total, P.lanes, P.simds, epw);
-      for (int m = RS_MAX_ROBOTS; m >= 2; --m) {  // the longest steps first
+      for (int m = RS_MAX_ROBOTS; m >= 2; --m) {  // the largest teams first
         tile_base[m] = tb;
         tb += (total[m] + epw[m] - 1) / epw[m];
       }

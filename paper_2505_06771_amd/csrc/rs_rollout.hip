@@ -84,8 +84,12 @@ extern "C" rs_status rollout(rs_ctx *ctx, const rs_params *p, const rs_batch *b,
   // fewer envs per wavefront make a shorter step: 4.5 -> 2.3 us at 96 x 6 (12
   // -> 96 wavefronts), 3.9 -> 3.0 us at 2048 x 8 (256 -> 1024). Above 32 lanes
   // the tiles of the split kernel run one after the other, and with two
-  // wavefronts per SIMD full ones win (4.1 against 5.5 us at 4096 x 8 with 512
-  // and 2048 wavefronts).
+  // wavefronts per SIMD full ones win. A step at 4096 x 8 with 512 (full), 1024
+  // and 2048 wavefronts: 3.9, 3.4 and 5.2 us; 6000 x 8 with 750 and 1500: 3.9 and
+  // 5.8; 4096 x 3 with 256, 512, 1024 and 2048: 3.2, 2.4, 2.1 and 3.7; 2048 x 12
+  // with 512, 1024 and 2048: 6.3, 5.2 and 7.7. Calls with qp_stats take full
+  // wavefronts (no counting kernels with split ones), so a small batch's step is
+  // up to twice as long in them.
   const int full = 64 / G, simds = 4 * ctx->num_cus;
   A.epw = full;
   if (!qp_stats)
