@@ -586,6 +586,9 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
       });
       gargmax_payload<G>(best, bid, bcx, bcy, bb);
       if (bid < 0) {
+        // a command that is not finite violates no row either, and leaves no
+        // residual that a maximum shows
+        if (group_any<G>(!(tabs(ux) + tabs(uy) < BIG), lane)) { out.status = 2; break; }
         if (settled) break;  // optimal
         T size;
         const T left = refine(size);
