@@ -38,10 +38,13 @@ HIPCC_FLAGS = [
 # one wavefront per SIMD waits for each line it enters, and where its blocks fall
 # moves its time by 3% (one FP64 env of 4 robots, 1000 steps: 1.14 ms unaligned,
 # 1.12 ms so, with other code around it 1.11 to 1.16; 43690 x 3 rollout 704.6 and
-# 701.7 us, 16384 x 8 595.7 and 594.5).
+# 701.7 us, 16384 x 8 595.7 and 594.5). rs_lib.hip also without register
+# allocation across calls, so that what its rare out-of-line solvers use does not
+# weigh on the kernels (the same FP64 steps 1.124 and 1.102 ms; FP64 certificates
+# of 16 robots 101.9 and 102.4 us, the other calls alike).
 ALIGN_BLOCKS = ["-mllvm", "-align-all-nofallthru-blocks=6"]
 FILE_FLAGS = {
-    "rs_lib.hip": ALIGN_BLOCKS,
+    "rs_lib.hip": [*ALIGN_BLOCKS, "-mllvm", "-enable-ipra=0"],
     "rs_rollout.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp", *ALIGN_BLOCKS],
     "rs_rollout_split.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
 }

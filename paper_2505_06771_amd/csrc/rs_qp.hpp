@@ -744,15 +744,19 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
 
 // The dual active-set method once more, from the box clip, with the Gram system
 // of the active pair rows over the coordinates that no active bound fixes,
-// factored anew on every step (serially, every lane of the group alike): for
-// what the general solver did not solve. Its inverse holds the bounds as rows
+// factored anew on every step (column by column, each lane two rows): for what
+// the general solver did not solve. Its inverse holds the bounds as rows
 // of their own, so a pair row of which the bounds leave only a sliver (two
 // robots held along their line of centres, met by the small component across
 // it) is too close to dependent on them; without the bounds it is an ordinary
 // row. An overlapping pair held at the walls, met by 4e-6 m/s across: called
 // infeasible in FP32 below 3e-5 rad off the axis without this.
-// A verdict of "infeasible" stands unless such a row (under 0.1% of its squared
-// norm free) is among the active ones or entering; "not solved" never does. Signature and `packed` as qp_general;
+// A verdict of "infeasible" stands unless such a row (free in less of its squared
+// norm than some hundred units of rounding) is among the active ones or
+// entering; "not solved" never does. It is bound by the latency of a solve's
+// 50 to 100 steps, each of q^2 / 2 fused products and 3q LDS round trips (6000
+// strewn envs of 16 robots, FP32, with a few such solves among them: 1.16 ms,
+// 2.73 with every lane factoring the whole system). Signature and `packed` as qp_general;
 // groups whose in_lds is not 3 pass through. fpb, fdx, fdy: the row that could
 // not enter.
 template <typename T, int G>
@@ -764,6 +768,7 @@ __device__ __noinline__ QPLoopOut<T> qp_factored(LdsScratch<T, G> *sh, int lane,
   typedef typename QPRow<T>::vec Row;
   typedef __attribute__((address_space(3))) Row LdsRow;
   typedef __attribute__((address_space(3))) T LdsT;
+  constexpr int S = 2;  // rows per lane: i and i + G
   const T BIG = big_v<T>();
   LdsRow *rows = sh->row;
   LdsT *lam = sh->lam, *L = sh->H;
@@ -795,7 +800,7 @@ __device__ __noinline__ QPLoopOut<T> qp_factored(LdsScratch<T, G> *sh, int lane,
       const T xx = w.y * w.y, yy = w.z * w.z;
       const T left = over(freex, freey, (int)w.x & 255, xx, yy) +
                      over(freex, freey, (int)w.x >> 8, xx, yy);
-      solve = solve || (left > T(0) && left < T(0.002) * (xx + yy));  // |c|^2 = 2 (xx + yy)
+      solve = solve || (left > T(0) && left < T(200) * eps_v<T>() * (xx + yy));  // |c|^2 / 2
     }
     out.q = 0;
   }
@@ -853,7 +858,10 @@ __device__ __noinline__ QPLoopOut<T> qp_factored(LdsScratch<T, G> *sh, int lane,
         }
       }
       gargmax<G>(best, bid);
-      if (bid < 0) break;  // optimal
+      if (bid < 0) {  // optimal
+        if (group_any<G>(!(tabs(ux) + tabs(uy) < BIG), lane)) status = 2;
+        break;
+      }
       if (++steps > cap) { status = 2; break; }
       // the entering row: coefficients (-cx, -cy) at robot pa, (cx, cy) at pb; a
       // bound: minus its unit normal, pb = kNoRobot
@@ -888,32 +896,64 @@ __device__ __noinline__ QPLoopOut<T> qp_factored(LdsScratch<T, G> *sh, int lane,
           if (sb == tb) acc += over(freex, freey, sb, xx, yy);
           return acc;
         };
-        // Cholesky factor of the active rows, then r = G^-1 (C c) in the work column
+        // Cholesky factor of the active rows, column by column, my rows i and i + G
         bool chol_ok = true;
-        for (int a = 0; a < q && chol_ok; ++a) {
-          const Row w = rows[a];
-          for (int b = 0; b <= a; ++b) {
-            T v = gram(rows[b], (int)w.x & 255, (int)w.x >> 8, w.y, w.z);
-            for (int k = 0; k < b; ++k) v -= L[tri(a, k)] * L[tri(b, k)];
-            if (a == b) {
-              chol_ok = v > T(0);
-              if (chol_ok) L[tri(a, a)] = sqrt_t(v);
-            } else {
-              L[tri(a, b)] = v / L[tri(b, b)];
+        for (int b = 0; b < q && chol_ok; ++b) {
+          const Row w = rows[b];
+          T v[S], d = T(0);
+#pragma unroll
+          for (int s = 0; s < S; ++s) {
+            const int a = i + s * G;
+            v[s] = T(0);
+            if (a >= b && a < q) {
+              v[s] = gram(rows[a], (int)w.x & 255, (int)w.x >> 8, w.y, w.z);
+              for (int k = 0; k < b; ++k) v[s] -= L[tri(a, k)] * L[tri(b, k)];
             }
+            d = b / G == s ? v[s] : d;
           }
+          d = __shfl(d, base + (b & (G - 1)), 64);
+          chol_ok = d > T(0);
+          const T root = sqrt_t(d);
+#pragma unroll
+          for (int s = 0; s < S; ++s) {
+            const int a = i + s * G;
+            if (a >= b && a < q) L[tri(a, b)] = a == b ? root : v[s] / root;
+          }
+          wave_lds_fence();
         }
         if (!chol_ok) { status = 2; break; }
+        // r = G^-1 (C c): my rows' values in g, the solved one passed round; r is
+        // left in the work column
+        T g[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          g[s] = i + s * G < q ? gram(rows[i + s * G], pa, pb, cx, cy) : T(0);
+        auto solved = [&](int a) {
+          return __shfl(a < G ? g[0] : g[S - 1], base + (a & (G - 1)), 64) / L[tri(a, a)];
+        };
         for (int a = 0; a < q; ++a) {
-          T g = gram(rows[a], pa, pb, cx, cy);
-          for (int k = 0; k < a; ++k) g -= L[tri(a, k)] * work(k);
-          work(a) = g / L[tri(a, a)];
+          const T x = solved(a);
+#pragma unroll
+          for (int s = 0; s < S; ++s) {
+            const int k = i + s * G;
+            if (k == a) g[s] = x;
+            else if (k > a && k < q) g[s] -= L[tri(k, a)] * x;
+          }
         }
         for (int a = q - 1; a >= 0; --a) {
-          T v = work(a);
-          for (int k = a + 1; k < q; ++k) v -= L[tri(k, a)] * work(k);
-          work(a) = v / L[tri(a, a)];
+          const T x = solved(a);
+#pragma unroll
+          for (int s = 0; s < S; ++s) {
+            const int k = i + s * G;
+            if (k == a) g[s] = x;
+            else if (k < a) g[s] -= L[tri(a, k)] * x;
+          }
         }
+        wave_lds_fence();
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          if (i + s * G < q) work(i + s * G) = g[s];
+        wave_lds_fence();
         // the row less its part in the active ones, at my robot: along free
         // coordinates the step, along fixed ones the change of my bounds
         const int sg = (i == pb) - (i == pa);
@@ -935,9 +975,11 @@ __device__ __noinline__ QPLoopOut<T> qp_factored(LdsScratch<T, G> *sh, int lane,
         // blocking row: the first active multiplier to reach zero
         T t1 = BIG;
         int drop = -1;  // pair slot, or 1024 + 2 robot + coordinate
-        for (int a = 0; a < q; ++a) {
-          const T ra = work(a), ratio = qdiv(lam[a], ra);
-          if (ra > eps_r && ratio < t1) { t1 = ratio; drop = a; }
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const int k = i + s * G;
+          const T ratio = k < q ? qdiv(lam[k], g[s]) : T(0);
+          if (k < q && g[s] > eps_r && ratio < t1) { t1 = ratio; drop = k; }
         }
         if (rfx > eps_r) {
           const T ratio = qdiv(mux, rfx);
@@ -958,14 +1000,19 @@ __device__ __noinline__ QPLoopOut<T> qp_factored(LdsScratch<T, G> *sh, int lane,
           ux -= t * zx;
           uy -= t * zy;
         }
-        for (int a = 0; a < q; ++a) lam[a] = lam[a] - t * work(a);
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          if (i + s * G < q) lam[i + s * G] -= t * g[s];
+        wave_lds_fence();
         mux -= t * rfx;
         muy -= t * rfy;
         lam_p += t;
         if (full) {
           if (pair) {
-            rows[q] = (Row){T(pa | pb << 8), cx, cy, T(0)};
-            lam[q] = lam_p;
+            if (i == 0) {
+              rows[q] = (Row){T(pa | pb << 8), cx, cy, T(0)};
+              lam[q] = lam_p;
+            }
             ++q;
             int owner, kk;
             pair_owner_g<G>(pa, pb, owner, kk);
@@ -986,12 +1033,13 @@ __device__ __noinline__ QPLoopOut<T> qp_factored(LdsScratch<T, G> *sh, int lane,
           int owner, kk;
           pair_owner_g<G>(id & 255, id >> 8, owner, kk);
           if (i == owner) own_act &= ~(1u << kk);
-          for (int a = drop; a + 1 < q; ++a) {
-            rows[a] = rows[a + 1];
-            lam[a] = lam[a + 1];
-          }
           --q;
+          if (i == 0 && drop != q) {  // the last row takes its place
+            rows[drop] = rows[q];
+            lam[drop] = lam[q];
+          }
         }
+        wave_lds_fence();
         if (++steps > cap) { status = 2; break; }
       }
     }
