@@ -338,7 +338,7 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
   if (i < q0) lam[i] = hl;
   // --- geometry of the owned pairs (the scan's formulas) ----------------------
   T cdx[KH], cdy[KH], cb[KH], crn[KH];
-  int cpid[KH];
+  uint32_t open_k = 0;  // bit K: my rotation-K pair can be violated and is not active
   static_for<1, KH + 1>([&](auto kc) {
     constexpr int K = decltype(kc)::value;
     const T pxj = grot<G, K>(px, lane), pyj = grot<G, K>(py, lane);
@@ -355,9 +355,8 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
     cdy[K - 1] = dy;
     cb[K - 1] = bb;
     crn[K - 1] = d2 > T(0) ? T(0.35355339059327373) * rsqrt_t(d2) : T(0);
-    cpid[K - 1] = (cand && d2 > T(0)) ? ((ia ? i : j) << 4 | (ia ? j : i)) : -1;
+    if (cand && d2 > T(0)) open_k |= 1u << K;
   });
-  uint32_t own_act = 0;  // bit K: my rotation-K pair is active
 
   // --- active bounds into the slots after the pairs, then H row by row --------
   int q;
@@ -381,7 +380,7 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
       const int id = (int)rows[s].x;
       int owner, kk;
       pair_owner_g<G>(id & 255, id >> 8, owner, kk);
-      if (i == owner) own_act |= 1u << kk;
+      if (i == owner) open_k &= ~(1u << kk);
     }
   }
   // product of H's row k with the work column of the first n rows
@@ -463,10 +462,12 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
   // command and multipliers from the active rows: one correction of the
   // multipliers by H times the rows' residuals. Returns the largest residual
   // over its row's norm that was left after it, and in `size` the largest sum
-  // of magnitudes that a coordinate of the command was formed from: a residual
-  // cannot fall below its rounding, in whatever unit the speeds are. (Formed
-  // here, in the sum that it belongs to: a loop of its own cost the solver's
-  // registers, and 16384 x 16 steps 50%.)
+  // of magnitudes that a robot's command was formed from: a residual cannot
+  // fall below its rounding, in whatever unit the speeds are. (One sum, formed
+  // beside the command: the solver's registers are counted. Beyond 194 of them
+  // at 8 lanes the Predator-Prey rollouts spill more in their step loop, 200
+  // took 6% off 16384 x 6; beyond 256 at 16 lanes a SIMD holds one wavefront,
+  // which took 50% off 16384 x 16 steps.)
   auto refine = [&](T &size) {
     T left = T(0);
     for (int pass = 0; pass < 2; ++pass) {
@@ -474,17 +475,16 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
       for (int s = 0; s < S; ++s)
         if (i + s * G < q) work(i + s * G) = lam[i + s * G];
       wave_lds_fence();
-      T vx = uhx, vy = uhy, ax = tabs(uhx), ay = tabs(uhy);
+      T vx = uhx, vy = uhy, mag = tabs(uhx) + tabs(uhy);
 #pragma unroll 4
       for (int a = 0; a < q; ++a) {
         const Row w = rows[a];
         const T f = T((i == ((int)w.x >> 8)) - (i == ((int)w.x & 255))) * w.w;
         vx -= f * w.y;
         vy -= f * w.z;
-        ax += tabs(f * w.y);
-        ay += tabs(f * w.z);
+        mag += tabs(f) * (tabs(w.y) + tabs(w.z));
       }
-      size = on ? tmax(ax, ay) : T(0);
+      size = on ? mag : T(0);
       ux = on ? vx : ux;
       uy = on ? vy : uy;
       const T bx = fx > 0 ? hix : lox, by = fy > 0 ? hiy : loy;
@@ -536,9 +536,9 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
   // rebuild() and refine(): the solver is called from kernels that fill the
   // instruction cache, and its size shows in their time.
   bool stale = true, again = false;
-  // the entering row: a pair (ra < rb, 2 D) or a bound
+  // the entering row (its id as the table holds it): a pair or a bound
   bool pend = carry;
-  int ra = (int)p.x & 255, rb = (int)p.x >> 8;
+  int rid = (int)p.x;
   T cx = p.y, cy = p.z, rhs = p.w;
   while (true) {
     if (stale) {
@@ -567,23 +567,28 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
           bb = (bid & 2) ? ((bid & 1) ? -loy : hiy) : ((bid & 1) ? -lox : hix);
         }
       }
+      int bk = 0;
       static_for<1, KH + 1>([&](auto kc) {
         constexpr int K = decltype(kc)::value;
         const T uxj = grot<G, K>(ux, lane), uyj = grot<G, K>(uy, lane);
-        if (cpid[K - 1] >= 0 && !((own_act >> K) & 1u)) {
+        if ((open_k >> K) & 1u) {
           const bool ia = i < ((i + K) & (G - 1));
           const T dux = ia ? uxj - ux : ux - uxj;
           const T duy = ia ? uyj - uy : uy - uyj;
           const T sn = (T(2) * (cdx[K - 1] * dux + cdy[K - 1] * duy) - cb[K - 1]) * crn[K - 1];
           if (sn > best) {
             best = sn;
-            bid = cpid[K - 1];
+            bk = K;
             bcx = T(2) * cdx[K - 1];
             bcy = T(2) * cdy[K - 1];
             bb = cb[K - 1];
           }
         }
       });
+      if (bk > 0) {
+        const int j = (i + bk) & (G - 1);
+        bid = min(i, j) << 4 | max(i, j);
+      }
       gargmax_payload<G>(best, bid, bcx, bcy, bb);
       if (bid < 0) {
         // a command that is not finite violates no row either, and leaves no
@@ -599,8 +604,7 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
         continue;
       }
       if (++out.iters > cap) { out.status = 2; break; }
-      ra = bid < 256 ? bid >> 4 : (bid - 256) >> 2;
-      rb = bid < 256 ? bid & 15 : kNoRobot;
+      rid = bid < 256 ? bid >> 4 | (bid & 15) << 8 : (bid - 256) >> 2 | kNoRobot << 8;
       cx = bcx;
       cy = bcy;
       rhs = bb;
@@ -608,6 +612,7 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
       pend = true;
     }
     // --- one step toward the entering row -------------------------------------
+    const int ra = rid & 255, rb = rid >> 8;
     const bool p_pair = rb != kNoRobot;
     T zx, zy, zz;
     direction(q, ra, rb, cx, cy, zx, zy, zz);
@@ -644,7 +649,7 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
     if (full) {
       grow(q, zz);
       if (i == 0) {
-        rows[q] = (Row){T(ra | rb << 8), cx, cy, T(0)};
+        rows[q] = (Row){T(rid), cx, cy, T(0)};
         lam[q] = lam_p;
       }
       wave_lds_fence();
@@ -652,7 +657,7 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
       if (p_pair) {
         int owner, kk;
         pair_owner_g<G>(ra, rb, owner, kk);
-        if (i == owner) own_act |= 1u << kk;
+        if (i == owner) open_k &= ~(1u << kk);
       } else if (i == ra) {
         // (cx, cy) is minus the normal: negative at an upper bound
         if (cx != T(0)) { fx = cx < T(0) ? 1 : -1; ux = cx < T(0) ? hix : lox; }
@@ -670,7 +675,7 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
       } else {
         int owner, kk;
         pair_owner_g<G>(wa, wb, owner, kk);
-        if (i == owner) own_act &= ~(1u << kk);
+        if (i == owner) open_k |= 1u << kk;
       }
       const int last = q - 1;
       const T ihd = T(1) / H[tri(drop, drop)];
@@ -734,7 +739,7 @@ __device__ __forceinline__ void qp_general_solve(LdsScratch<T, G> *sh, int lane,
     for (int c = 0; c < kHandback; ++c) hw[c * G] = v[c];
     wave_lds_fence();
     out.in_lds = 3;
-    enter = (Row){T(ra | rb << 8), cx, cy, T(0)};
+    enter = (Row){T(rid), cx, cy, T(0)};
   }
   out.ux = ux;
   out.uy = uy;
@@ -1069,11 +1074,16 @@ __device__ __noinline__ QPLoopOut<T> qp_general(LdsScratch<T, G> *sh, int lane, 
                                                 T loy, T hiy, bool seed, int iters, int fpb, T fl1,
                                                 T fdx, T fdy, T rs2, T gamma, T vmax4, T tol_add,
                                                 T eps_z, T eps_r, int qp_cap, bool want_rows) {
-  QPLoopOut<T> out{ux, uy, (packed >> 8) & 255, iters, packed >> 16, packed & 255};
+  QPLoopOut<T> out;
   typename QPRow<T>::vec p{};
-  if (out.in_lds != 0)
-    qp_general_solve<T, G>(sh, lane, N, out.in_lds == 2, out, rs2, gamma, vmax4, tol_add, eps_z,
-                           eps_r, qp_cap, p);
+  const int run = packed & 255;
+  if (run != 0) {
+    out = QPLoopOut<T>{ux, uy, 0, iters, packed >> 16, run};
+    qp_general_solve<T, G>(sh, lane, N, run == 2, out, rs2, gamma, vmax4, tol_add, eps_z, eps_r,
+                           qp_cap, p);
+  } else {
+    out = QPLoopOut<T>{ux, uy, (packed >> 8) & 255, iters, packed >> 16, 0};
+  }
   if (__ballot(out.in_lds == 3) != 0)  // wavefront-uniform: a tail call
     [[clang::musttail]] return qp_factored<T, G>(
         sh, lane, out.in_lds | out.status << 8 | out.q << 16, N, true, T(0), T(0), out.ux, out.uy,
